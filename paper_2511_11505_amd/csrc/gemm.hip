@@ -10,7 +10,7 @@
 // accumulation) with both operand tiles staged through a ring of LDS slots
 // by direct global->LDS copies; few-row passes stream the weights straight
 // into registers.  The launcher picks the tile variant per pass from the
-// shape.  fp32 runs on the vector ALUs.
+// shape.  fp32 runs on the fp32 matrix cores (gemm_f32.hip).
 //
 // Groups have ragged row counts known only on the device.  Every workgroup
 // rebuilds the per-group m-tile prefix from group_offsets in LDS, then walks
@@ -24,96 +24,17 @@
 #include <type_traits>
 
 #include "common.hpp"
+#include "gemm_common.hpp"
 #include "internal.hpp"
 
 namespace fs {
 namespace {
-
-constexpr int kMaxGroups = 512;
-constexpr int kXcd = 8;
-enum { MODE_GATEUP = 0, MODE_DOWN = 1 };
 
 // SiLU(g) * u for the bf16 epilogues, whose result is rounded to bf16: the
 // hardware exponential and reciprocal (about 1 ulp each in fp32) replace the
 // IEEE division, which costs ten instructions per element.
 __device__ __forceinline__ float swiglu_bf16_epi(float g, float u) {
   return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u;
-}
-
-// Group offsets and the exclusive prefix of m-tiles per group, in LDS.
-template <int NT, int BM>
-__device__ void sched_setup(const int32_t* __restrict__ goff, int G, int64_t m_total,
-                            int* s_goff, int* s_tpre, int* s_wtot) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // Offsets are clamped to [0, m_total]: rows past the host bound are never
-  // read or written, so a short bound cannot overrun the H workspace.
-  for (int g = tid; g <= G; g += NT) {
-    int v = goff ? goff[g] : (g == 0 ? 0 : (int)m_total);
-    s_goff[g] = v < 0 ? 0 : (v > (int)m_total ? (int)m_total : v);
-  }
-  __syncthreads();
-  constexpr int IPT = (kMaxGroups + 1 + NT - 1) / NT;
-  int cnt[IPT];
-  int local = 0;
-#pragma unroll
-  for (int i = 0; i < IPT; ++i) {
-    const int g = tid * IPT + i;
-    const int c = (g < G && s_goff[g + 1] > s_goff[g]) ? (s_goff[g + 1] - s_goff[g] + BM - 1) / BM : 0;
-    cnt[i] = c;
-    local += c;
-  }
-  int incl = local;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int v = __shfl_up(incl, o, FS_WAVE);
-    if (lane >= o) incl += v;
-  }
-  if (lane == 63) s_wtot[wave] = incl;
-  __syncthreads();
-  int pre = 0;
-  for (int w = 0; w < wave; ++w) pre += s_wtot[w];
-  int run = pre + incl - local;
-#pragma unroll
-  for (int i = 0; i < IPT; ++i) {
-    const int g = tid * IPT + i;
-    if (g <= G) s_tpre[g] = run;
-    run += cnt[i];
-  }
-  __syncthreads();
-}
-
-// Largest g in [0, G) with nn * tpre[g] <= L.
-__device__ __forceinline__ int find_group(const int* s_tpre, int G, int nn, int64_t L) {
-  int lo = 0, hi = G - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if ((int64_t)nn * s_tpre[mid] <= L)
-      lo = mid;
-    else
-      hi = mid - 1;
-  }
-  return lo;
-}
-
-// find_group for a workgroup's items, which come in increasing order: the
-// answer is at least lo (the previous item's group), and most often lo or
-// lo + 1, so two LDS reads usually settle it before any binary search.
-__device__ __forceinline__ int find_group_from(const int* s_tpre, int G, int nn, int64_t L, int lo) {
-  if (lo + 1 < G && (int64_t)nn * s_tpre[lo + 1] <= L) {
-    ++lo;
-    if (lo + 1 < G && (int64_t)nn * s_tpre[lo + 1] <= L) {
-      int hi = G - 1;
-      ++lo;
-      while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if ((int64_t)nn * s_tpre[mid] <= L)
-          lo = mid;
-        else
-          hi = mid - 1;
-      }
-    }
-  }
-  return lo;
 }
 
 // ---------------------------------------------------------------- bf16 MFMA
@@ -294,76 +215,6 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_kernel(
 // The epilogue stages the output tile through LDS so that global stores are
 // whole 16-byte row chunks.
 
-typedef __attribute__((address_space(3))) void lds_void_t;
-typedef __attribute__((address_space(1))) void glb_void_t;
-
-// One direct global->LDS load of 16 bytes per lane: lane l's bytes land at
-// LDS address lds + 16 * l, where lds is the wave's destination as a
-// wave-uniform 32-bit LDS address (kept in SGPRs by the caller, so a copy
-// needs no address-space conversion or lane broadcast).  Issued as inline
-// assembly so that the compiler does not add a conservative wait for every
-// outstanding DMA before each LDS read; the kernels order them themselves
-// with explicit vmcnt waits and barriers.  M0 carries the LDS address and has
-// no other user in these kernels.
-__device__ __forceinline__ void dma16_at(const void* g, unsigned lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
-               :
-               : "s"(lds), "v"(g)
-               : "memory");
-}
-
-// The same with the global address split into a wave-uniform 64-bit base
-// (SGPRs) and a 32-bit per-lane byte offset: the weight rows of a wave's DMAs
-// share one base, so they hold two VGPRs of offsets instead of a 64-bit
-// pointer per DMA.
-__device__ __forceinline__ void dma16_sb(const void* base, unsigned off, unsigned lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-               :
-               : "s"(lds), "v"(off), "s"(base)
-               : "memory");
-}
-
-// A pointer made wave-uniform (held in SGPRs): lane 0's value.
-template <typename T>
-__device__ __forceinline__ T* uniform_ptr(T* p) {
-  const uint64_t v = (uint64_t)(uintptr_t)p;
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return (T*)(uintptr_t)(((uint64_t)hi << 32) | lo);
-}
-
-// A 16-byte load marked non-temporal (the streaming hint), for the expert
-// weights that the fragment-ordered decode passes read exactly once.
-// DeepSeek-V3-shaped decode, routed gate/up 266 -> 239 us (6.43 TB/s, 0.80
-// of HBM), down 142 -> 140 us, step 0.531 -> 0.508 ms (same-box A/B).  The
-// 64-row shared expert's weight-streaming kernels were slower with it
-// (gate/up 28 -> 30 us, down 17 -> 18 us) and keep ordinary loads.
-template <typename V>
-__device__ __forceinline__ V ld_stream(const void* p) {
-  typedef int v4i __attribute__((ext_vector_type(4)));
-  static_assert(sizeof(V) == 16, "16-byte loads");
-  const v4i v = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(p));
-  return __builtin_bit_cast(V, v);
-}
-
-// LDS address of a __shared__ location as a wave-uniform 32-bit value.
-__device__ __forceinline__ unsigned lds_addr(const void* p) {
-  return __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(const lds_void_t*)p);
-}
-
-// s_waitcnt with only vmcnt constrained (gfx9 encoding).
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8));
-}
-
-__device__ __forceinline__ void barrier_nofence() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
 // ---------------------------------------------------------------- bf16 MFMA, interleaved
 // Same tiles, ring and swizzle as above, with the memory work hidden under
 // the MFMAs by a rolling pipeline over 16-wide K steps.  Each step first
@@ -429,11 +280,6 @@ __device__ __forceinline__ void barrier_nofence() {
 // DeepSeek-V3-shaped prefill 3.92 -> 3.83 ms, DeepSeek-V2-Lite-shaped
 // 0.925 -> 0.893 ms (same-box A/B).  (With four waves of 64 x 128 it had
 // been slower on every pass.)
-
-__device__ __forceinline__ void wait_lgkm0() {
-  // lgkmcnt(0), vmcnt and expcnt unconstrained
-  __builtin_amdgcn_s_waitcnt((0xF) | (0x3 << 14) | (0x7 << 4) | (0x0 << 8));
-}
 
 typedef int int32x8 __attribute__((ext_vector_type(8)));
 
@@ -1390,10 +1236,6 @@ __global__ __launch_bounds__(256) void stream_reduce_kernel(
   }
 }
 
-// ---------------------------------------------------------------- fp32 VALU
-// 64 x 64 tiles, 256 threads, 4 rows x 4 columns per thread.  For gate/up a
-// tile holds 32 gate and the matching 32 up columns; a thread owns 2 H
-// columns (their gate and up values).
 // ---------------------------------------------------------------- bf16 MFMA, skinny down pass
 // The down pass of one group of at most 64 rows (a decode batch's shared
 // expert): workgroup w owns 32 output columns over the whole K, so d / 32
@@ -1485,122 +1327,6 @@ __global__ __launch_bounds__(256) void gemm_bf16_skinny_down_kernel(
     const int grow = row_base + r;
     const int64_t orow = rows ? (int64_t)rows[grow] : (int64_t)grow;
     C[orow * ldc + c0 + c] = f2bf(y);
-  }
-}
-
-template <int MODE>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A,
-                                                       const int32_t* __restrict__ rows,
-                                                       const int32_t* __restrict__ goff, int G,
-                                                       int64_t m_total,
-                                                       const float* __restrict__ B, int K,
-                                                       int NOUT, float* __restrict__ C,
-                                                       int ldc) {
-  constexpr int BM = 64, BN = 64, BK = 16, NT = 256;
-  constexpr int NCOL = (MODE == MODE_GATEUP) ? BN / 2 : BN;
-  __shared__ int s_goff[kMaxGroups + 1];
-  __shared__ int s_tpre[kMaxGroups + 1];
-  __shared__ int s_wtot[NT / 64];
-  __shared__ __align__(16) float As[BK][BM + 4];
-  __shared__ __align__(16) float Bs[BK][BN + 4];
-
-  const int tid = threadIdx.x;
-  const int tm = tid % 16, tn = tid / 16;
-  sched_setup<NT, BM>(goff, G, m_total, s_goff, s_tpre, s_wtot);
-  const int nn = NOUT / NCOL;
-  const int64_t total = (int64_t)nn * s_tpre[G];
-  const int64_t per_xcd = (total + kXcd - 1) / kXcd;
-  const int64_t xcd_base = (int64_t)(blockIdx.x % kXcd) * per_xcd;
-  const int64_t stride = gridDim.x / kXcd;
-  const size_t bstride = (size_t)((MODE == MODE_GATEUP) ? 2 * NOUT : NOUT) * K;
-
-  for (int64_t j = blockIdx.x / kXcd; j < per_xcd; j += stride) {
-    const int64_t L = xcd_base + j;
-    if (L >= total) break;
-    const int g = find_group(s_tpre, G, nn, L);
-    const int Tg = s_tpre[g + 1] - s_tpre[g];
-    const int64_t local = L - (int64_t)nn * s_tpre[g];
-    const int nt = (int)(local / Tg), mt = (int)(local % Tg);
-    const int row_base = s_goff[g], rows_g = s_goff[g + 1] - row_base;
-    const int m0 = mt * BM, n0 = nt * NCOL;
-    const float* Bg = B + (size_t)g * bstride;
-
-    // one 16-byte chunk of A and of B per thread per K step
-    const int lr = tid / 4, lk = (tid % 4) * 4;
-    const bool va = m0 + lr < rows_g;
-    const int grow_l = row_base + (va ? m0 + lr : 0);
-    const int64_t src = (MODE == MODE_GATEUP && rows) ? (int64_t)rows[grow_l] : (int64_t)grow_l;
-    const float* pa = A + src * K + lk;
-    int wrow;
-    if (MODE == MODE_GATEUP)
-      wrow = (lr < BN / 2) ? n0 + lr : NOUT + n0 + (lr - BN / 2);
-    else
-      wrow = n0 + lr;
-    const float* pb = Bg + (size_t)wrow * K + lk;
-
-    float acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int c = 0; c < 4; ++c) acc[i][c] = 0.f;
-
-    float4 ra = va ? *reinterpret_cast<const float4*>(pa) : make_float4(0, 0, 0, 0);
-    float4 rb = *reinterpret_cast<const float4*>(pb);
-    for (int k0 = 0; k0 < K; k0 += BK) {
-      __syncthreads();
-      As[lk + 0][lr] = ra.x;
-      As[lk + 1][lr] = ra.y;
-      As[lk + 2][lr] = ra.z;
-      As[lk + 3][lr] = ra.w;
-      Bs[lk + 0][lr] = rb.x;
-      Bs[lk + 1][lr] = rb.y;
-      Bs[lk + 2][lr] = rb.z;
-      Bs[lk + 3][lr] = rb.w;
-      __syncthreads();
-      if (k0 + BK < K) {
-        ra = va ? *reinterpret_cast<const float4*>(pa + k0 + BK) : make_float4(0, 0, 0, 0);
-        rb = *reinterpret_cast<const float4*>(pb + k0 + BK);
-      }
-#pragma unroll
-      for (int kk = 0; kk < BK; ++kk) {
-        const float4 av = *reinterpret_cast<const float4*>(&As[kk][tm * 4]);
-        float bv[4];
-        if (MODE == MODE_GATEUP) {
-          bv[0] = Bs[kk][tn * 2];
-          bv[1] = Bs[kk][tn * 2 + 1];
-          bv[2] = Bs[kk][BN / 2 + tn * 2];
-          bv[3] = Bs[kk][BN / 2 + tn * 2 + 1];
-        } else {
-          const float4 b4 = *reinterpret_cast<const float4*>(&Bs[kk][tn * 4]);
-          bv[0] = b4.x;
-          bv[1] = b4.y;
-          bv[2] = b4.z;
-          bv[3] = b4.w;
-        }
-        const float a4[4] = {av.x, av.y, av.z, av.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int c = 0; c < 4; ++c) acc[i][c] = fmaf(a4[i], bv[c], acc[i][c]);
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int m = m0 + tm * 4 + i;
-      if (m >= rows_g) continue;
-      const int grow = row_base + m;
-      if (MODE == MODE_GATEUP) {
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-          const float gt = acc[i][c], up = acc[i][c + 2];
-          C[(size_t)grow * ldc + n0 + tn * 2 + c] = gt / (1.0f + expf(-gt)) * up;
-        }
-      } else {
-        const int64_t orow = rows ? (int64_t)rows[grow] : (int64_t)grow;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) C[orow * ldc + n0 + tn * 4 + c] = acc[i][c];
-      }
-    }
   }
 }
 
@@ -1968,15 +1694,13 @@ hipError_t launch_grouped_ffn(int dtype, int G, int ffn, int d, const void* in,
     if (profile) prof_end(pd, s);
   } else {
     float* H = reinterpret_cast<float*>(ws);
-    const int64_t g1 = grid_for(max_rows, G, 64, ffn / 32);
     if (profile) prof_begin(pg, s);
-    launch_k(gemm_f32_kernel<MODE_GATEUP>, (unsigned)g1, 256, 0, s,
-        (const float*)in, rows_in, goff, G, max_rows, (const float*)w_gate_up, d, ffn, H, ffn);
+    launch_gemm_f32(true, (const float*)in, rows_in, goff, G, max_rows, (const float*)w_gate_up, d,
+                    ffn, H, ffn, num_cus(), s);
     if (profile) prof_end(pg, s);
-    const int64_t g2 = grid_for(max_rows, G, 64, d / 64);
     if (profile) prof_begin(pd, s);
-    launch_k(gemm_f32_kernel<MODE_DOWN>, (unsigned)g2, 256, 0, s,
-        H, rows_out, goff, G, max_rows, (const float*)w_down, ffn, d, (float*)out, d);
+    launch_gemm_f32(false, H, rows_out, goff, G, max_rows, (const float*)w_down, ffn, d,
+                    (float*)out, d, num_cus(), s);
     if (profile) prof_end(pd, s);
   }
   return hipGetLastError();
@@ -2073,9 +1797,8 @@ hipError_t launch_dense_linear(int dtype, int m, int n, int kdim, const void* a,
     launch_k(gemm_bf16_kernel<MODE_DOWN, kBM, kBN, kBK, 2, 2>, (unsigned)g, 256, 0, s,
         (const bf16_t*)a, nullptr, nullptr, 1, m, (const bf16_t*)w, kdim, n, (bf16_t*)out, n);
   } else {
-    const int64_t g = grid_for(m, 1, 64, n / 64);
-    launch_k(gemm_f32_kernel<MODE_DOWN>, (unsigned)g, 256, 0, s,
-        (const float*)a, nullptr, nullptr, 1, m, (const float*)w, kdim, n, (float*)out, n);
+    launch_gemm_f32(false, (const float*)a, nullptr, nullptr, 1, m, (const float*)w, kdim, n,
+                    (float*)out, n, num_cus(), s);
   }
   return hipGetLastError();
 }

@@ -1,0 +1,79 @@
+"""GPU parity of the grouped FFN and the dense linear at the edges of their
+tiles and dispatch rules: row counts around fragment and tile heights, empty
+groups, widths that leave a part tile, gathered and in-order rows; element by
+element against the oracle.  fp32 results differ from the 64-bit oracle by
+sums of at most 2048 rounded products (about sqrt(2048) 2^-24 = 3e-6 of the
+rms); bf16 ones by the rounding of H and of the output."""
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2511_11505_amd import _lib as L
+from tests._util import TOL, f64, rel_err
+from workloads import CONFIGS
+
+pytestmark = [pytest.mark.gpu,
+              pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")]
+DEV = "cuda"
+TORCH = {"f32": torch.float32, "bf16": torch.bfloat16}
+
+
+def ffn_case(dtype, counts, d, F, gather, seed=0):
+    """Inputs of a grouped FFN: (X, rows or None, goff, wgu, wd, n_src)."""
+    counts = np.array(counts)
+    G, M = len(counts), int(counts.sum())
+    goff = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    gen = torch.Generator(device=DEV).manual_seed(seed + d + 3 * F + G)
+    n_src = M + 5
+    X = torch.randn((n_src, d), generator=gen, device=DEV).to(TORCH[dtype])
+    wgu = (0.05 * torch.randn((G, 2 * F, d), generator=gen, device=DEV)).to(TORCH[dtype])
+    wd = (0.05 * torch.randn((G, d, F), generator=gen, device=DEV)).to(TORCH[dtype])
+    rows = torch.randperm(n_src, generator=gen, device=DEV)[:M].to(torch.int32) if gather else None
+    return X, rows, goff, wgu, wd, n_src
+
+
+def check_ffn(dtype, X, rows, goff, wgu, wd, out):
+    G, M = len(goff) - 1, int(goff[-1])
+    rr = rows.cpu().numpy() if rows is not None else np.arange(M)
+    Xn, outn = f64(X), f64(out)
+    for gi in range(G):
+        sel = rr[goff[gi]:goff[gi + 1]]
+        if len(sel):
+            want = oracle.swiglu(Xn[sel], f64(wgu[gi]), f64(wd[gi]))
+            assert rel_err(outn[sel], want) <= TOL[dtype], f"group {gi} of {len(sel)} rows"
+    assert np.all(np.isnan(outn[np.setdiff1d(np.arange(X.shape[0]), rr)]))
+
+
+EDGES = [1, 15, 16, 17, 0, 32, 33, 48, 49, 63, 64, 65, 80, 0, 127, 130]
+
+
+# fp32: 64-row tiles of 64 weight rows (few tiles) and of 128 (at least two
+# tiles per CU, counted from the row bound), K of one part to many blocks
+@pytest.mark.parametrize("counts,d,F,gather,slack", [
+    (EDGES, 128, 64, True, 0), (EDGES, 384, 192, False, 9), (EDGES * 3, 1792, 832, True, 0),
+    ([70], 2048, 64, False, 0)])
+def test_ffn_f32_edges(counts, d, F, gather, slack):
+    X, rows, goff, wgu, wd, n_src = ffn_case("f32", counts, d, F, gather)
+    M = int(goff[-1])
+    bound = M + slack
+    out = torch.full((n_src, d), float("nan"), device=DEV)
+    desc = L.make_desc(CONFIGS["tiny"].scaled(hidden=d, ffn=F, dtype="f32"))
+    ws = torch.empty((L.fs_workspace_size(desc, L.FS_OP_GROUPED_FFN, bound, F),), dtype=torch.uint8,
+                     device=DEV)
+    L.fs_grouped_expert_ffn(desc, len(counts), F, X, rows, torch.from_numpy(goff).to(DEV), bound,
+                            wgu, wd, out, ws)
+    torch.cuda.synchronize()
+    check_ffn("f32", X, rows, goff, wgu, wd, out)
+
+
+@pytest.mark.parametrize("m,n,kd", [(1, 64, 64), (65, 192, 128), (129, 4096, 320), (1030, 8256, 64)])
+def test_dense_linear_f32_edges(m, n, kd):
+    gen = torch.Generator(device=DEV).manual_seed(m + n)
+    a = torch.randn((m, kd), generator=gen, device=DEV)
+    w = 0.05 * torch.randn((n, kd), generator=gen, device=DEV)
+    out = torch.full((m, n), float("nan"), device=DEV)
+    L.fs_dense_linear(L.FS_F32, m, n, kd, a, w, out)
+    torch.cuda.synchronize()
+    assert rel_err(out, oracle.dense_linear(f64(a), f64(w))) <= TOL["f32"]
