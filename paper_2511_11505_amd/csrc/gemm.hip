@@ -10,7 +10,7 @@
 // accumulation) with both operand tiles staged through a ring of LDS slots
 // by direct global->LDS copies; few-row passes stream the weights straight
 // into registers.  The launcher picks the tile variant per pass from the
-// shape.  fp32 runs on the fp32 matrix cores (gemm_f32.hip).
+// shape.  fp32 runs on the fp32 matrix cores (gemm_r64.hip).
 //
 // Groups have ragged row counts known only on the device.  Every workgroup
 // rebuilds the per-group m-tile prefix from group_offsets in LDS, then walks
@@ -18,8 +18,6 @@
 // space is cut into eight contiguous ranges, one per XCD (workgroups are
 // dispatched round-robin over the XCDs), so tiles sharing a weight panel or
 // a row panel run under one L2.
-
-#include <stdlib.h>
 
 #include <type_traits>
 
@@ -29,179 +27,6 @@
 
 namespace fs {
 namespace {
-
-// SiLU(g) * u for the bf16 epilogues, whose result is rounded to bf16: the
-// hardware exponential and reciprocal (about 1 ulp each in fp32) replace the
-// IEEE division, which costs ten instructions per element.
-__device__ __forceinline__ float swiglu_bf16_epi(float g, float u) {
-  return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u;
-}
-
-// ---------------------------------------------------------------- bf16 MFMA
-template <int MODE, int BM, int BN, int BK, int WAVES_M, int WAVES_N>
-__global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_kernel(
-    const bf16_t* __restrict__ A, const int32_t* __restrict__ rows,
-    const int32_t* __restrict__ goff, int G, int64_t m_total, const bf16_t* __restrict__ B, int K,
-    int NOUT, bf16_t* __restrict__ C, int ldc) {
-  constexpr int NT = 64 * WAVES_M * WAVES_N;
-  constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N;
-  constexpr int TM = WTM / 32, TN = WTN / 32;
-  constexpr int LDK = BK + 8;  // LDS row stride in bf16: 16-byte skew per row
-  constexpr int CPR = BK / 8;  // 16-byte chunks per tile row
-  constexpr int ACH = BM * CPR / NT, BCH = BN * CPR / NT;
-  constexpr int NCOL = (MODE == MODE_GATEUP) ? BN / 2 : BN;
-  constexpr int STAGE = (BM + BN) * LDK;
-  static_assert(BM * CPR % NT == 0 && BN * CPR % NT == 0, "tile loads must divide evenly");
-  static_assert(MODE != MODE_GATEUP || TN % 2 == 0, "gate/up tiles come in pairs");
-
-  __shared__ int s_goff[kMaxGroups + 1];
-  __shared__ int s_tpre[kMaxGroups + 1];
-  __shared__ int s_wtot[NT / 64];
-  __shared__ __align__(16) bf16_t lds[2 * STAGE];
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WAVES_N, wn = wave % WAVES_N;
-  sched_setup<NT, BM>(goff, G, m_total, s_goff, s_tpre, s_wtot);
-
-  const int nn = NOUT / NCOL;
-  const int64_t total = (int64_t)nn * s_tpre[G];
-  const int64_t per_xcd = (total + kXcd - 1) / kXcd;
-  const int64_t xcd_base = (int64_t)(blockIdx.x % kXcd) * per_xcd;
-  const int64_t stride = gridDim.x / kXcd;
-  const int KT = K / BK;
-  const size_t bstride = (size_t)((MODE == MODE_GATEUP) ? 2 * NOUT : NOUT) * K;
-
-  for (int64_t j = blockIdx.x / kXcd; j < per_xcd; j += stride) {
-    const int64_t L = xcd_base + j;
-    if (L >= total) break;
-    const int g = find_group(s_tpre, G, nn, L);
-    const int Tg = s_tpre[g + 1] - s_tpre[g];
-    const int64_t local = L - (int64_t)nn * s_tpre[g];
-    const int nt = (int)(local / Tg), mt = (int)(local % Tg);
-    const int row_base = s_goff[g], rows_g = s_goff[g + 1] - row_base;
-    const int m0 = mt * BM, n0 = nt * NCOL;
-    const bf16_t* Bg = B + (size_t)g * bstride;
-
-    const bf16_t* pa[ACH];
-    bool va[ACH];
-#pragma unroll
-    for (int i = 0; i < ACH; ++i) {
-      const int c = tid + i * NT;
-      const int r = c / CPR, kc = (c % CPR) * 8;
-      const int m = m0 + r;
-      va[i] = m < rows_g;
-      const int grow = row_base + (va[i] ? m : 0);
-      const int64_t src = (MODE == MODE_GATEUP && rows) ? (int64_t)rows[grow] : (int64_t)grow;
-      pa[i] = A + src * K + kc;
-    }
-    const bf16_t* pb[BCH];
-#pragma unroll
-    for (int i = 0; i < BCH; ++i) {
-      const int c = tid + i * NT;
-      const int r = c / CPR, kc = (c % CPR) * 8;
-      int wrow;
-      if (MODE == MODE_GATEUP)
-        wrow = (r < BN / 2) ? n0 + r : NOUT + n0 + (r - BN / 2);
-      else
-        wrow = n0 + r;
-      pb[i] = Bg + (size_t)wrow * K + kc;
-    }
-
-    floatx16 acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int jn = 0; jn < TN; ++jn)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[i][jn][v] = 0.f;
-
-    uint4 ra[ACH], rb[BCH];
-    auto gload = [&](int k0) {
-#pragma unroll
-      for (int i = 0; i < ACH; ++i) ra[i] = va[i] ? ld16(pa[i] + k0) : make_uint4(0, 0, 0, 0);
-#pragma unroll
-      for (int i = 0; i < BCH; ++i) rb[i] = ld16(pb[i] + k0);
-    };
-    auto lstore = [&](int buf) {
-      bf16_t* As = lds + buf * STAGE;
-      bf16_t* Bs = As + BM * LDK;
-#pragma unroll
-      for (int i = 0; i < ACH; ++i) {
-        const int c = tid + i * NT;
-        st16(As + (c / CPR) * LDK + (c % CPR) * 8, ra[i]);
-      }
-#pragma unroll
-      for (int i = 0; i < BCH; ++i) {
-        const int c = tid + i * NT;
-        st16(Bs + (c / CPR) * LDK + (c % CPR) * 8, rb[i]);
-      }
-    };
-
-    gload(0);
-    for (int kt = 0; kt < KT; ++kt) {
-      lstore(kt & 1);
-      __syncthreads();
-      if (kt + 1 < KT) gload((kt + 1) * BK);
-      const bf16_t* As = lds + (kt & 1) * STAGE;
-      const bf16_t* Bs = As + BM * LDK;
-#pragma unroll
-      for (int ks = 0; ks < BK / 16; ++ks) {
-        const int kofs = ks * 16 + (lane >> 5) * 8;
-        bf16x8 af[TM], bfr[TN];
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-          const int r = wm * WTM + i * 32 + (lane & 31);
-          af[i] = *reinterpret_cast<const bf16x8*>(As + r * LDK + kofs);
-        }
-#pragma unroll
-        for (int jn = 0; jn < TN; ++jn) {
-          int br;
-          if (MODE == MODE_GATEUP)
-            br = (jn < TN / 2) ? wn * (WTN / 2) + jn * 32
-                               : BN / 2 + wn * (WTN / 2) + (jn - TN / 2) * 32;
-          else
-            br = wn * WTN + jn * 32;
-          bfr[jn] = *reinterpret_cast<const bf16x8*>(Bs + (br + (lane & 31)) * LDK + kofs);
-        }
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int jn = 0; jn < TN; ++jn)
-            acc[i][jn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], bfr[jn], acc[i][jn], 0,
-                                                                 0, 0);
-      }
-    }
-
-    // Epilogue.  Accumulator element v of lane l holds row
-    // 8*(v/4) + 4*(l/32) + v%4 and column l%32 of its 32x32 tile.
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int m = m0 + wm * WTM + i * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-        if (m >= rows_g) continue;
-        const int grow = row_base + m;
-        if (MODE == MODE_GATEUP) {
-#pragma unroll
-          for (int jn = 0; jn < TN / 2; ++jn) {
-            const float gt = acc[i][jn][v], up = acc[i][jn + TN / 2][v];
-            const float h = swiglu_bf16_epi(gt, up);
-            const int col = n0 + wn * (WTN / 2) + jn * 32 + (lane & 31);
-            C[(size_t)grow * ldc + col] = f2bf(h);
-          }
-        } else {
-          const int64_t orow = rows ? (int64_t)rows[grow] : (int64_t)grow;
-#pragma unroll
-          for (int jn = 0; jn < TN; ++jn) {
-            const int col = n0 + wn * WTN + jn * 32 + (lane & 31);
-            C[orow * ldc + col] = f2bf(acc[i][jn][v]);
-          }
-        }
-      }
-    }
-    __syncthreads();  // LDS stages are reused by the next tile
-  }
-}
 
 // ---------------------------------------------------------------- bf16 MFMA, DMA ring
 // BM x BN x 64 tiles, four waves (2 x 2), each wave BM/2 x BN/2 through
@@ -1330,8 +1155,6 @@ __global__ __launch_bounds__(256) void gemm_bf16_skinny_down_kernel(
   }
 }
 
-constexpr int kBM = 128, kBN = 128, kBK = 64;
-
 int64_t grid_for(int64_t max_rows, int G, int BM, int nn) {
   int64_t upper = (cdiv64(max_rows, BM) + G) * nn;
   upper = ((upper + kXcd - 1) / kXcd) * kXcd;
@@ -1486,6 +1309,41 @@ bool use_stream(int dtype, int64_t max_rows, int G, int ffn, int d) {
   return ring_tiles < 256;
 }
 
+// Kernel of one pass (gate/up: NOUT = F, K = d; down: NOUT = d, K = F).
+enum PassKind { PASS_R64, PASS_STREAM, PASS_RING };
+
+// The 64-row tiles (gemm_r64.hip) take fp32, widths the ring's tiles do not
+// divide, and, of the bf16 passes that others could take as well:
+// - grouped FFNs of at most 48 rows a group, hidden size below 4096: a
+//   128-row tile is then mostly padding.  64 groups, d 2048, F 1408, gate/up
+//   + down: 6 rows a group 146 + 68 us on the ring, 137 + 65 us on 64-row
+//   tiles; 31 rows 160 + 71 and 148 + 70; but 66 rows 169 + 76 and 177 + 95,
+//   and 32 groups of 16 rows, d 7168, F 2048: 295 + 163 and 301 + 179;
+// - one dense group whose 128 x 256 ring tiles would leave CUs idle and K be
+//   split, for K below 4096 (us with the split and its reduction -> on 64-row
+//   tiles): d 2048, F 2816, gate/up + down, 333 rows 42 + 24 -> 22 + 16, 1365
+//   rows 64 + 60 -> 58 + 38; down of d 7168, F 2048: 64 rows 18 -> 16, 333
+//   rows 52 -> 34, 1000 rows 69 -> 62.  A long K needs the split: gate/up of
+//   that shape, 64 rows 30 -> 41, 1000 rows 135 -> 141;
+// - unless the rows fit one tile and the weight tiles alone occupy enough CUs
+//   (more than a quarter): d 5120, F 8192, 64 rows: gate/up 60 -> 39 (256
+//   tiles), down 59 -> 43 (80 tiles).
+PassKind pass_kind(int dtype, bool gateup, int64_t max_rows, int G, int ffn, int d) {
+  if (dtype != 1) return PASS_R64;
+  const int NOUT = gateup ? ffn : d, K = gateup ? d : ffn;
+  const bool stream = use_stream(dtype, max_rows, G, ffn, d);
+  if (G == 1) {
+    const int64_t ring_tiles = cdiv64(max_rows, 128) * (NOUT / (gateup ? 128 : 256));
+    if (ring_tiles < num_cus() &&
+        (K < 4096 || (max_rows <= 64 && NOUT / (gateup ? 32 : 64) > num_cus() / 4)))
+      return PASS_R64;
+  } else if (!stream && max_rows <= (int64_t)48 * G && d < 4096) {
+    return PASS_R64;
+  }
+  if (stream) return PASS_STREAM;
+  return ffn % 128 == 0 && d % 256 == 0 ? PASS_RING : PASS_R64;
+}
+
 // One FP8 GEMM pass on 128 x 256 tiles, eight waves of 64 x 64 (as bf16:
 // routed gate/up of the DeepSeek-V3-shaped prefill 1000 -> 955 us, down
 // 660 -> 616 us against four waves of 64 x 128).  Measured on the routed
@@ -1601,108 +1459,53 @@ hipError_t launch_grouped_ffn(int dtype, int G, int ffn, int d, const void* in,
                               const void* w_gate_up, const void* w_down, void* out, void* ws,
                               hipStream_t s, int prof_gate_up) {
   const bool profile = prof_gate_up >= 0;
-  const int pg = prof_gate_up, pd = prof_gate_up + 1;
   if (max_rows <= 0) return hipSuccess;
-  if (use_stream(dtype, max_rows, G, ffn, d)) {
-    bf16_t* H = reinterpret_cast<bf16_t*>(ws);
-    float* P = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) +
-                                        ((size_t)max_rows * ffn * 2 + 255) / 256 * 256);
-    const size_t pbytes = stream_partial_bytes(dtype, max_rows, ffn, d);
-    // 64 activation rows per pass when the groups average more than 32
-    const bool wide = max_rows > (int64_t)32 * G;
-    // gate/up: 32 H columns per workgroup; down: 64 output columns
-    {
-      const int kt = d / 64, sp = stream_splits(max_rows, G, 2 * ffn, d, pbytes);
-      const int kps = (int)cdiv64(kt, sp), spe = (int)cdiv64(kt, kps);
-      if (profile) prof_begin(pg, s);
-      const unsigned grid = (unsigned)((int64_t)G * (ffn / 32) * spe);
-      if (wide)
-        launch_k(gemm_bf16_stream_kernel<MODE_GATEUP, 4>, grid, 64, 0, s,
-            (const bf16_t*)in, rows_in, goff, G, max_rows, (const bf16_t*)w_gate_up, d, ffn, H, ffn,
-            P, spe, kps);
-      else
-        launch_k(gemm_bf16_stream_kernel<MODE_GATEUP, 2>, grid, 64, 0, s,
-            (const bf16_t*)in, rows_in, goff, G, max_rows, (const bf16_t*)w_gate_up, d, ffn, H, ffn,
-            P, spe, kps);
-      if (spe > 1)
-        launch_k(stream_reduce_kernel<MODE_GATEUP>,
-                 (unsigned)std::min<int64_t>(cdiv64(max_rows * ffn, 256), 8192), 256, 0, s, P,
-                 rows_in, goff, G, max_rows, ffn, spe, H, ffn);
-      if (profile) prof_end(pg, s);
-    }
-    // one group of at most 64 rows: the skinny down pass where K allows it
-    if (G == 1 && max_rows <= 64 && ffn % 512 == 0 && d % 32 == 0) {
-      if (profile) prof_begin(pd, s);
-      launch_k(gemm_bf16_skinny_down_kernel, (unsigned)(d / 32), 256, 0, s, H, rows_out, goff,
-               max_rows, (const bf16_t*)w_down, ffn, d, (bf16_t*)out, d);
-      if (profile) prof_end(pd, s);
+  // H, then the fp32 partials of the passes that split K
+  float* P = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) +
+                                      ((size_t)max_rows * ffn * 2 + 255) / 256 * 256);
+  const size_t pbytes = stream_partial_bytes(dtype, max_rows, ffn, d);
+  auto pass = [&](auto M, const void* a, const int32_t* rows, const void* w, int K, int NOUT, void* c) {
+    constexpr int MODE = decltype(M)::value;
+    constexpr bool gateup = MODE == MODE_GATEUP;
+    const PassKind kind = pass_kind(dtype, gateup, max_rows, G, ffn, d);
+    if (kind == PASS_R64) {
+      launch_gemm_r64(dtype, gateup, a, rows, goff, G, max_rows, w, K, NOUT, c, NOUT, num_cus(), s);
+    } else if (kind == PASS_RING) {
+      const int v = tile_choice(!gateup, NOUT);
+      KSplit sp;
+      if (v == 5)
+        sp = make_split(ring_splits(gateup, 128, max_rows, G, K / 64, NOUT, pbytes), K / 64, P);
+      gemm_pass<MODE>(v, (const bf16_t*)a, rows, goff, G, max_rows, (const bf16_t*)w, K, NOUT,
+                      (bf16_t*)c, NOUT, s, sp);
+      reduce_split<MODE>(sp, rows, goff, G, max_rows, NOUT, (bf16_t*)c, NOUT, s);
+    } else if (!gateup && G == 1 && max_rows <= 64 && K % 512 == 0 && NOUT % 32 == 0) {
+      // one group of at most 64 rows: the skinny down pass where K allows it
+      launch_k(gemm_bf16_skinny_down_kernel, (unsigned)(NOUT / 32), 256, 0, s, (const bf16_t*)a, rows,
+               goff, max_rows, (const bf16_t*)w, K, NOUT, (bf16_t*)c, NOUT);
     } else {
-      const int kt = ffn / 64, sp = stream_splits(max_rows, G, d, ffn, pbytes);
+      // weight rows per workgroup: 32 gate and 32 up, or 64 output columns;
+      // 64 activation rows per pass when the groups average more than 32
+      const int kt = K / 64, sp = stream_splits(max_rows, G, gateup ? 2 * NOUT : NOUT, K, pbytes);
       const int kps = (int)cdiv64(kt, sp), spe = (int)cdiv64(kt, kps);
-      if (profile) prof_begin(pd, s);
-      const unsigned grid = (unsigned)((int64_t)G * (d / 64) * spe);
-      if (wide)
-        launch_k(gemm_bf16_stream_kernel<MODE_DOWN, 4>, grid, 64, 0, s, H, rows_out, goff, G,
-                 max_rows, (const bf16_t*)w_down, ffn, d, (bf16_t*)out, d, P, spe, kps);
+      const unsigned grid = (unsigned)((int64_t)G * (NOUT / (gateup ? 32 : 64)) * spe);
+      if (max_rows > (int64_t)32 * G)
+        launch_k(gemm_bf16_stream_kernel<MODE, 4>, grid, 64, 0, s, (const bf16_t*)a, rows, goff, G,
+                 max_rows, (const bf16_t*)w, K, NOUT, (bf16_t*)c, NOUT, P, spe, kps);
       else
-        launch_k(gemm_bf16_stream_kernel<MODE_DOWN, 2>, grid, 64, 0, s, H, rows_out, goff, G,
-                 max_rows, (const bf16_t*)w_down, ffn, d, (bf16_t*)out, d, P, spe, kps);
+        launch_k(gemm_bf16_stream_kernel<MODE, 2>, grid, 64, 0, s, (const bf16_t*)a, rows, goff, G,
+                 max_rows, (const bf16_t*)w, K, NOUT, (bf16_t*)c, NOUT, P, spe, kps);
       if (spe > 1)
-        launch_k(stream_reduce_kernel<MODE_DOWN>,
-                 (unsigned)std::min<int64_t>(cdiv64(max_rows * d, 256), 8192), 256, 0, s, P,
-                 rows_out, goff, G, max_rows, d, spe, (bf16_t*)out, d);
-      if (profile) prof_end(pd, s);
+        launch_k(stream_reduce_kernel<MODE>,
+                 (unsigned)std::min<int64_t>(cdiv64(max_rows * NOUT, 256), 8192), 256, 0, s, P, rows,
+                 goff, G, max_rows, NOUT, spe, (bf16_t*)c, NOUT);
     }
-  } else if (dtype == 1 && ffn % 128 == 0 && d % 256 == 0) {
-    bf16_t* H = reinterpret_cast<bf16_t*>(ws);
-    float* P = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) +
-                                        ((size_t)max_rows * ffn * 2 + 255) / 256 * 256);
-    const size_t pbytes = stream_partial_bytes(dtype, max_rows, ffn, d);
-    auto split_of = [&](int v, bool gateup, int K, int NOUT) {
-      if (v != 5) return KSplit{};
-      return make_split(ring_splits(gateup, 128, max_rows, G, K / 64, NOUT, pbytes), K / 64, P);
-    };
-    if (profile) prof_begin(pg, s);
-    {
-      const int v = tile_choice(false, ffn);
-      const KSplit sp = split_of(v, true, d, ffn);
-      gemm_pass<MODE_GATEUP>(v, (const bf16_t*)in, rows_in, goff, G, max_rows,
-                             (const bf16_t*)w_gate_up, d, ffn, H, ffn, s, sp);
-      reduce_split<MODE_GATEUP>(sp, rows_in, goff, G, max_rows, ffn, H, ffn, s);
-    }
-    if (profile) prof_end(pg, s);
-    if (profile) prof_begin(pd, s);
-    {
-      const int v = tile_choice(true, d);
-      const KSplit sp = split_of(v, false, ffn, d);
-      gemm_pass<MODE_DOWN>(v, H, rows_out, goff, G, max_rows, (const bf16_t*)w_down, ffn, d,
-                           (bf16_t*)out, d, s, sp);
-      reduce_split<MODE_DOWN>(sp, rows_out, goff, G, max_rows, d, (bf16_t*)out, d, s);
-    }
-    if (profile) prof_end(pd, s);
-  } else if (dtype == 1) {
-    bf16_t* H = reinterpret_cast<bf16_t*>(ws);
-    const int64_t g1 = grid_for(max_rows, G, kBM, ffn / (kBN / 2));
-    if (profile) prof_begin(pg, s);
-    launch_k(gemm_bf16_kernel<MODE_GATEUP, kBM, kBN, kBK, 2, 2>, (unsigned)g1, 256, 0, s,
-        (const bf16_t*)in, rows_in, goff, G, max_rows, (const bf16_t*)w_gate_up, d, ffn, H, ffn);
-    if (profile) prof_end(pg, s);
-    const int64_t g2 = grid_for(max_rows, G, kBM, d / kBN);
-    if (profile) prof_begin(pd, s);
-    launch_k(gemm_bf16_kernel<MODE_DOWN, kBM, kBN, kBK, 2, 2>, (unsigned)g2, 256, 0, s,
-        H, rows_out, goff, G, max_rows, (const bf16_t*)w_down, ffn, d, (bf16_t*)out, d);
-    if (profile) prof_end(pd, s);
-  } else {
-    float* H = reinterpret_cast<float*>(ws);
-    if (profile) prof_begin(pg, s);
-    launch_gemm_f32(true, (const float*)in, rows_in, goff, G, max_rows, (const float*)w_gate_up, d,
-                    ffn, H, ffn, num_cus(), s);
-    if (profile) prof_end(pg, s);
-    if (profile) prof_begin(pd, s);
-    launch_gemm_f32(false, H, rows_out, goff, G, max_rows, (const float*)w_down, ffn, d,
-                    (float*)out, d, num_cus(), s);
-    if (profile) prof_end(pd, s);
-  }
+  };
+  if (profile) prof_begin(prof_gate_up, s);
+  pass(std::integral_constant<int, MODE_GATEUP>{}, in, rows_in, w_gate_up, d, ffn, ws);
+  if (profile) prof_end(prof_gate_up, s);
+  if (profile) prof_begin(prof_gate_up + 1, s);
+  pass(std::integral_constant<int, MODE_DOWN>{}, ws, rows_out, w_down, ffn, d, out);
+  if (profile) prof_end(prof_gate_up + 1, s);
   return hipGetLastError();
 }
 
@@ -1787,19 +1590,15 @@ hipError_t launch_grouped_ffn_fo_fp8(int G, int ffn, int d, const uint8_t* x, co
 hipError_t launch_dense_linear(int dtype, int m, int n, int kdim, const void* a, const void* w,
                                void* out, hipStream_t s) {
   if (m <= 0) return hipSuccess;
-  if (dtype == 1 && n % 128 == 0) {
-    // the LDS-ring kernels as one group of m rows (128 x 128 tiles when n is
-    // not a multiple of 256)
+  // one group of m rows: 64-row tiles where the ring's would leave CUs idle
+  // (see pass_kind), else the LDS ring (128 x 128 tiles when n is not a
+  // multiple of 256)
+  const int64_t ring_tiles = cdiv64(m, 128) * (n / (n % 256 == 0 ? 256 : 128));
+  if (dtype != 1 || (ring_tiles < num_cus() && kdim < 4096))
+    launch_gemm_r64(dtype, false, a, nullptr, nullptr, 1, m, w, kdim, n, out, n, num_cus(), s);
+  else
     gemm_pass<MODE_DOWN>(tile_choice(true, n), (const bf16_t*)a, nullptr, nullptr, 1,
                          m, (const bf16_t*)w, kdim, n, (bf16_t*)out, n, s);
-  } else if (dtype == 1) {
-    const int64_t g = grid_for(m, 1, kBM, n / kBN);
-    launch_k(gemm_bf16_kernel<MODE_DOWN, kBM, kBN, kBK, 2, 2>, (unsigned)g, 256, 0, s,
-        (const bf16_t*)a, nullptr, nullptr, 1, m, (const bf16_t*)w, kdim, n, (bf16_t*)out, n);
-  } else {
-    launch_gemm_f32(false, (const float*)a, nullptr, nullptr, 1, m, (const float*)w, kdim, n,
-                    (float*)out, n, num_cus(), s);
-  }
   return hipGetLastError();
 }
 

@@ -86,11 +86,11 @@ hipError_t launch_grouped_ffn_fp8(int n_groups, int ffn, int d, const uint8_t* x
                                   const uint8_t* w_gate_up, const float* s_gate_up,
                                   const uint8_t* w_down, const float* s_down, void* out,
                                   void* ws, hipStream_t s, int prof_gate_up);
-// One fp32 pass (gemm_f32.hip): gate/up with SwiGLU (rows gathered) or down
-// (rows scattered); cus: compute units to fill.
-void launch_gemm_f32(bool gateup, const float* A, const int32_t* rows, const int32_t* goff, int G,
-                     int64_t m_total, const float* B, int K, int NOUT, float* C, int ldc, int cus,
-                     hipStream_t s);
+// One pass on 64-row tiles (gemm_r64.hip; dtype 0 fp32, 1 bf16): gate/up with
+// SwiGLU (rows gathered) or down (rows scattered); cus: compute units to fill.
+void launch_gemm_r64(int dtype, bool gateup, const void* A, const int32_t* rows,
+                     const int32_t* goff, int G, int64_t m_total, const void* B, int K, int NOUT,
+                     void* C, int ldc, int cus, hipStream_t s);
 hipError_t launch_dense_linear(int dtype, int m, int n, int kdim, const void* a, const void* w,
                                void* out, hipStream_t s);
 // Expert weights in MFMA fragment order: n_mats row-major [rows, cols] bf16

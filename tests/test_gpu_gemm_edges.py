@@ -51,29 +51,39 @@ EDGES = [1, 15, 16, 17, 0, 32, 33, 48, 49, 63, 64, 65, 80, 0, 127, 130]
 
 # fp32: 64-row tiles of 64 weight rows (few tiles) and of 128 (at least two
 # tiles per CU, counted from the row bound), K of one part to many blocks
-@pytest.mark.parametrize("counts,d,F,gather,slack", [
-    (EDGES, 128, 64, True, 0), (EDGES, 384, 192, False, 9), (EDGES * 3, 1792, 832, True, 0),
-    ([70], 2048, 64, False, 0)])
-def test_ffn_f32_edges(counts, d, F, gather, slack):
-    X, rows, goff, wgu, wd, n_src = ffn_case("f32", counts, d, F, gather)
+# bf16: widths only these tiles take (K % 128 = 64 among them), short groups
+# and one dense group at widths the 128-row ring takes too, and the long-K
+# rule's row and tile counts
+@pytest.mark.parametrize("dtype,counts,d,F,gather,slack", [
+    ("f32", EDGES, 128, 64, True, 0), ("f32", EDGES, 384, 192, False, 9),
+    ("f32", EDGES * 3, 1792, 832, True, 0), ("f32", [70], 2048, 64, False, 0),
+    ("bf16", EDGES, 128, 64, True, 0), ("bf16", EDGES, 384, 192, True, 9),
+    ("bf16", EDGES * 3, 1792, 832, False, 0), ("bf16", EDGES * 2, 512, 256, True, 7),
+    ("bf16", [333], 512, 384, False, 0), ("bf16", [1], 256, 128, False, 0),
+    ("bf16", [2100], 1152, 704, False, 0), ("bf16", [64], 4096, 2176, False, 0),
+    ("bf16", [65], 4096, 2176, False, 0)])
+def test_ffn_edges(dtype, counts, d, F, gather, slack):
+    X, rows, goff, wgu, wd, n_src = ffn_case(dtype, counts, d, F, gather)
     M = int(goff[-1])
     bound = M + slack
-    out = torch.full((n_src, d), float("nan"), device=DEV)
-    desc = L.make_desc(CONFIGS["tiny"].scaled(hidden=d, ffn=F, dtype="f32"))
+    out = torch.full((n_src, d), float("nan"), device=DEV).to(TORCH[dtype])
+    desc = L.make_desc(CONFIGS["tiny"].scaled(hidden=d, ffn=F, dtype=dtype))
     ws = torch.empty((L.fs_workspace_size(desc, L.FS_OP_GROUPED_FFN, bound, F),), dtype=torch.uint8,
                      device=DEV)
     L.fs_grouped_expert_ffn(desc, len(counts), F, X, rows, torch.from_numpy(goff).to(DEV), bound,
                             wgu, wd, out, ws)
     torch.cuda.synchronize()
-    check_ffn("f32", X, rows, goff, wgu, wd, out)
+    check_ffn(dtype, X, rows, goff, wgu, wd, out)
 
 
-@pytest.mark.parametrize("m,n,kd", [(1, 64, 64), (65, 192, 128), (129, 4096, 320), (1030, 8256, 64)])
-def test_dense_linear_f32_edges(m, n, kd):
+@pytest.mark.parametrize("dtype,m,n,kd", [
+    ("f32", 1, 64, 64), ("f32", 65, 192, 128), ("f32", 129, 4096, 320), ("f32", 1030, 8256, 64),
+    ("bf16", 33, 640, 4032), ("bf16", 130, 384, 4096), ("bf16", 1000, 2048, 192)])
+def test_dense_linear_edges(dtype, m, n, kd):
     gen = torch.Generator(device=DEV).manual_seed(m + n)
-    a = torch.randn((m, kd), generator=gen, device=DEV)
-    w = 0.05 * torch.randn((n, kd), generator=gen, device=DEV)
-    out = torch.full((m, n), float("nan"), device=DEV)
-    L.fs_dense_linear(L.FS_F32, m, n, kd, a, w, out)
+    a = torch.randn((m, kd), generator=gen, device=DEV).to(TORCH[dtype])
+    w = (0.05 * torch.randn((n, kd), generator=gen, device=DEV)).to(TORCH[dtype])
+    out = torch.full((m, n), float("nan"), device=DEV).to(TORCH[dtype])
+    L.fs_dense_linear(L.FS_F32 if dtype == "f32" else L.FS_BF16, m, n, kd, a, w, out)
     torch.cuda.synchronize()
-    assert rel_err(out, oracle.dense_linear(f64(a), f64(w))) <= TOL["f32"]
+    assert rel_err(out, oracle.dense_linear(f64(a), f64(w))) <= TOL[dtype]
