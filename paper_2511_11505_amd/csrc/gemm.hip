@@ -1309,8 +1309,39 @@ bool use_stream(int dtype, int64_t max_rows, int G, int ffn, int d) {
   return ring_tiles < 256;
 }
 
+// Largest tile height of a pass on the 192-row tiles.  Of one dense group,
+// whose rows the host knows: the height whose rounds of tiles over the CUs
+// (each costing its rows, and a fixed part worth about 32) are shortest.
+// Routed groups take 192: their sizes, and so the rounds, are known on the
+// device only.
+int r192_height(int64_t max_rows, int G, int n_tiles) {
+  if (G > 1) return 192;
+  int best = 192;
+  int64_t best_cost = -1;
+  for (int h = 192; h >= 128; h -= 32) {
+    const int64_t t = cdiv64(max_rows, h), height = cdiv64(cdiv64(max_rows, t), 32) * 32;
+    const int64_t cost = cdiv64(t * n_tiles, num_cus()) * (height + 32);
+    if (best_cost < 0 || cost < best_cost) {
+      best_cost = cost;
+      best = h;
+    }
+  }
+  return best;
+}
+
+// The 192-row tiles take the passes whose groups average at least 112 rows and
+// whose 128-row ring tiles would give every CU one (below that the ring splits
+// K).  64 groups, d 2048, F 1408, gate/up + down: 96 rows a group 169 + 79 us
+// on the ring, 168 + 81 us on these tiles; 128 rows 216 + 114 and 180 + 87;
+// 384 rows 367 + 209 and 330 + 197.  32 groups of 1024 rows, d 7168, F 2048:
+// 1755 + 978 and 1670 + 829.  One group of 8192 rows, gate/up of d 5120,
+// F 8192: 1228 -> 998 us (1.38 PFLOP/s).
+bool r192_ok(int64_t max_rows, int G, int K, int64_t ring_tiles) {
+  return max_rows >= (int64_t)112 * G && ring_tiles >= num_cus() && K >= 256 && K % 128 == 0;
+}
+
 // Kernel of one pass (gate/up: NOUT = F, K = d; down: NOUT = d, K = F).
-enum PassKind { PASS_R64, PASS_STREAM, PASS_RING };
+enum PassKind { PASS_R64, PASS_STREAM, PASS_RING, PASS_R192 };
 
 // The 64-row tiles (gemm_r64.hip) take fp32, widths the ring's tiles do not
 // divide, and, of the bf16 passes that others could take as well:
@@ -1341,7 +1372,9 @@ PassKind pass_kind(int dtype, bool gateup, int64_t max_rows, int G, int ffn, int
     return PASS_R64;
   }
   if (stream) return PASS_STREAM;
-  return ffn % 128 == 0 && d % 256 == 0 ? PASS_RING : PASS_R64;
+  if (ffn % 128 != 0 || d % 256 != 0) return PASS_R64;
+  const int64_t ring_tiles = G * cdiv64(max_rows, (int64_t)128 * G) * (NOUT / (gateup ? 128 : 256));
+  return r192_ok(max_rows, G, K, ring_tiles) ? PASS_R192 : PASS_RING;
 }
 
 // One FP8 GEMM pass on 128 x 256 tiles, eight waves of 64 x 64 (as bf16:
@@ -1470,6 +1503,10 @@ hipError_t launch_grouped_ffn(int dtype, int G, int ffn, int d, const void* in,
     const PassKind kind = pass_kind(dtype, gateup, max_rows, G, ffn, d);
     if (kind == PASS_R64) {
       launch_gemm_r64(dtype, gateup, a, rows, goff, G, max_rows, w, K, NOUT, c, NOUT, num_cus(), s);
+    } else if (kind == PASS_R192) {
+      const int hmax = r192_height(max_rows, G, NOUT / (gateup ? 128 : 256));
+      (gateup ? launch_r192_gateup : launch_r192_down)(a, rows, goff, G, max_rows, w, K, NOUT, c, NOUT,
+                                                       num_cus(), hmax, s);
     } else if (kind == PASS_RING) {
       const int v = tile_choice(!gateup, NOUT);
       KSplit sp;
@@ -1591,11 +1628,14 @@ hipError_t launch_dense_linear(int dtype, int m, int n, int kdim, const void* a,
                                void* out, hipStream_t s) {
   if (m <= 0) return hipSuccess;
   // one group of m rows: 64-row tiles where the ring's would leave CUs idle
-  // (see pass_kind), else the LDS ring (128 x 128 tiles when n is not a
-  // multiple of 256)
+  // (see pass_kind), else the 192-row tiles, else the LDS ring (128 x 128
+  // tiles when n is not a multiple of 256)
   const int64_t ring_tiles = cdiv64(m, 128) * (n / (n % 256 == 0 ? 256 : 128));
   if (dtype != 1 || (ring_tiles < num_cus() && kdim < 4096))
     launch_gemm_r64(dtype, false, a, nullptr, nullptr, 1, m, w, kdim, n, out, n, num_cus(), s);
+  else if (n % 256 == 0 && r192_ok(m, 1, kdim, ring_tiles))
+    launch_r192_down(a, nullptr, nullptr, 1, m, w, kdim, n, out, n, num_cus(),
+                     r192_height(m, 1, n / 256), s);
   else
     gemm_pass<MODE_DOWN>(tile_choice(true, n), (const bf16_t*)a, nullptr, nullptr, 1,
                          m, (const bf16_t*)w, kdim, n, (bf16_t*)out, n, s);

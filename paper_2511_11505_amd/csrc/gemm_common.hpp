@@ -18,10 +18,11 @@ __device__ __forceinline__ float swiglu_bf16_epi(float g, float u) {
   return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u;
 }
 
-// Group offsets and the exclusive prefix of m-tiles per group, in LDS.
-template <int NT, int BM>
+// Group offsets and the exclusive prefix of m-tiles (of BM rows) per group, in
+// LDS.
+template <int NT>
 __device__ void sched_setup(const int32_t* __restrict__ goff, int G, int64_t m_total,
-                            int* s_goff, int* s_tpre, int* s_wtot) {
+                            int* s_goff, int* s_tpre, int* s_wtot, int BM) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // Offsets are clamped to [0, m_total]: rows past the host bound are never
   // read or written, so a short bound cannot overrun the H workspace.
@@ -58,6 +59,12 @@ __device__ void sched_setup(const int32_t* __restrict__ goff, int G, int64_t m_t
     run += cnt[i];
   }
   __syncthreads();
+}
+
+template <int NT, int BM>
+__device__ __forceinline__ void sched_setup(const int32_t* __restrict__ goff, int G, int64_t m_total,
+                                            int* s_goff, int* s_tpre, int* s_wtot) {
+  sched_setup<NT>(goff, G, m_total, s_goff, s_tpre, s_wtot, BM);
 }
 
 // Largest g in [0, G) with nn * tpre[g] <= L.

@@ -1,0 +1,13 @@
+// The gate/up pass of gemm_r192.hpp (a file of its own: each takes about a minute
+// to compile).
+#include "gemm_r192.hpp"
+
+namespace fs {
+
+void launch_r192_gateup(const void* A, const int32_t* rows, const int32_t* goff, int G,
+                    int64_t m_total, const void* B, int K, int NOUT, void* C, int ldc, int cus,
+                    int hmax, hipStream_t s) {
+  run_r192<MODE_GATEUP>(A, rows, goff, G, m_total, B, K, NOUT, C, ldc, cus, hmax, s);
+}
+
+}  // namespace fs

@@ -91,6 +91,15 @@ hipError_t launch_grouped_ffn_fp8(int n_groups, int ffn, int d, const uint8_t* x
 void launch_gemm_r64(int dtype, bool gateup, const void* A, const int32_t* rows,
                      const int32_t* goff, int G, int64_t m_total, const void* B, int K, int NOUT,
                      void* C, int ldc, int cus, hipStream_t s);
+// One bf16 pass on tiles of up to 192 x 256 (gemm_r192.hpp): K % 128 == 0, K >= 256,
+// NOUT % 128 == 0 (gate/up) or % 256 == 0 (down).
+// hmax: largest tile height, 128, 160 or 192 rows.
+void launch_r192_gateup(const void* A, const int32_t* rows, const int32_t* goff, int G,
+                        int64_t m_total, const void* B, int K, int NOUT, void* C, int ldc, int cus,
+                        int hmax, hipStream_t s);
+void launch_r192_down(const void* A, const int32_t* rows, const int32_t* goff, int G,
+                      int64_t m_total, const void* B, int K, int NOUT, void* C, int ldc, int cus,
+                      int hmax, hipStream_t s);
 hipError_t launch_dense_linear(int dtype, int m, int n, int kdim, const void* a, const void* w,
                                void* out, hipStream_t s);
 // Expert weights in MFMA fragment order: n_mats row-major [rows, cols] bf16

@@ -76,8 +76,40 @@ def test_ffn_edges(dtype, counts, d, F, gather, slack):
     check_ffn(dtype, X, rows, goff, wgu, wd, out)
 
 
+# 192-row tiles: every tile height (128 to 192 in steps of 32 and the short
+# tiles below), groups of one to several equal tiles, one band and more of
+# m-tiles, several tiles per workgroup, K of four blocks and more, row bounds
+# above the rows
+TALL = [192, 193, 130, 0, 97, 384, 385, 5, 161, 577, 224, 256]
+
+
+@pytest.mark.parametrize("counts,d,F,gather,slack", [
+    (TALL, 2048, 1408, True, 0), (TALL, 512, 3072, False, 31), (TALL * 2, 256, 2816, True, 0),
+    ([2048], 768, 2048, False, 0), ([3500, 1], 1280, 1408, True, 5), ([4100], 256, 1024, False, 0)])
+def test_ffn_tall_tiles(counts, d, F, gather, slack):
+    X, rows, goff, wgu, wd, n_src = ffn_case("bf16", counts, d, F, gather, seed=7)
+    bound = int(goff[-1]) + slack
+    out = torch.full((n_src, d), float("nan"), device=DEV).to(torch.bfloat16)
+    desc = L.make_desc(CONFIGS["tiny"].scaled(hidden=d, ffn=F, dtype="bf16"))
+    ws = torch.empty((L.fs_workspace_size(desc, L.FS_OP_GROUPED_FFN, bound, F),), dtype=torch.uint8,
+                     device=DEV)
+    L.fs_grouped_expert_ffn(desc, len(counts), F, X, rows, torch.from_numpy(goff).to(DEV), bound,
+                            wgu, wd, out, ws)
+    torch.cuda.synchronize()
+    check_ffn("bf16", X, rows, goff, wgu, wd, out)
+
+
+def test_tall_tile_heights():
+    """Equal heights cover a group: no tile is empty or taller than allowed."""
+    for hmax in (128, 160, 192):
+        rows = np.arange(1, 60000)
+        t = -(-rows // hmax)
+        h = ((rows + t - 1) // t + 31) & ~31
+        assert np.all(h <= hmax) and np.all((t - 1) * h < rows) and np.all(t * h >= rows)
+
+
 @pytest.mark.parametrize("dtype,m,n,kd", [
-    ("f32", 1, 64, 64), ("f32", 65, 192, 128), ("f32", 129, 4096, 320), ("f32", 1030, 8256, 64),
+    ("bf16", 2300, 3840, 256), ("bf16", 4097, 2048, 384), ("f32", 1, 64, 64), ("f32", 65, 192, 128), ("f32", 129, 4096, 320), ("f32", 1030, 8256, 64),
     ("bf16", 33, 640, 4032), ("bf16", 130, 384, 4096), ("bf16", 1000, 2048, 192)])
 def test_dense_linear_edges(dtype, m, n, kd):
     gen = torch.Generator(device=DEV).manual_seed(m + n)
