@@ -1314,12 +1314,12 @@ bool use_stream(int dtype, int64_t max_rows, int G, int ffn, int d) {
 // (each costing its rows, and a fixed part worth about 32) are shortest.
 // Routed groups take 192: their sizes, and so the rounds, are known on the
 // device only.
-int r192_height(int64_t max_rows, int G, int n_tiles) {
+int r192_height(int64_t max_rows, int G, int n_tiles, int unit = 32) {
   if (G > 1) return 192;
   int best = 192;
   int64_t best_cost = -1;
-  for (int h = 192; h >= 128; h -= 32) {
-    const int64_t t = cdiv64(max_rows, h), height = cdiv64(cdiv64(max_rows, t), 32) * 32;
+  for (int h = 192; h >= 128; h -= unit) {
+    const int64_t t = cdiv64(max_rows, h), height = cdiv64(cdiv64(max_rows, t), unit) * unit;
     const int64_t cost = cdiv64(t * n_tiles, num_cus()) * (height + 32);
     if (best_cost < 0 || cost < best_cost) {
       best_cost = cost;
@@ -1334,10 +1334,10 @@ int r192_height(int64_t max_rows, int G, int n_tiles) {
 // K).  64 groups, d 2048, F 1408, gate/up + down: 96 rows a group 169 + 79 us
 // on the ring, 168 + 81 us on these tiles; 128 rows 216 + 114 and 180 + 87;
 // 384 rows 367 + 209 and 330 + 197.  32 groups of 1024 rows, d 7168, F 2048:
-// 1755 + 978 and 1670 + 829.  One group of 8192 rows, gate/up of d 5120,
+// 1755 + 978 and 1690 + 829 (FP8 916 + 565 and 860 + 470).  One group of 8192 rows, gate/up of d 5120,
 // F 8192: 1228 -> 998 us (1.38 PFLOP/s).
-bool r192_ok(int64_t max_rows, int G, int K, int64_t ring_tiles) {
-  return max_rows >= (int64_t)112 * G && ring_tiles >= num_cus() && K >= 256 && K % 128 == 0;
+bool r192_ok(int64_t max_rows, int G, int k_blocks, int64_t ring_tiles) {
+  return max_rows >= (int64_t)112 * G && ring_tiles >= num_cus() && k_blocks >= 4;
 }
 
 // Kernel of one pass (gate/up: NOUT = F, K = d; down: NOUT = d, K = F).
@@ -1374,7 +1374,7 @@ PassKind pass_kind(int dtype, bool gateup, int64_t max_rows, int G, int ffn, int
   if (stream) return PASS_STREAM;
   if (ffn % 128 != 0 || d % 256 != 0) return PASS_R64;
   const int64_t ring_tiles = G * cdiv64(max_rows, (int64_t)128 * G) * (NOUT / (gateup ? 128 : 256));
-  return r192_ok(max_rows, G, K, ring_tiles) ? PASS_R192 : PASS_RING;
+  return r192_ok(max_rows, G, K / 64, ring_tiles) ? PASS_R192 : PASS_RING;
 }
 
 // One FP8 GEMM pass on 128 x 256 tiles, eight waves of 64 x 64 (as bf16:
@@ -1458,25 +1458,29 @@ hipError_t launch_grouped_ffn_fp8(int G, int ffn, int d, const uint8_t* x, const
                                       ((size_t)max_rows * 4 + 255) / 256 * 256);
   const size_t pbytes = split_partial_bytes(max_rows, ffn, d);
   bf16_t* Y = static_cast<bf16_t*>(out);
-  if (profile) prof_begin(prof_gate_up, s);
-  {
+  auto pass = [&](auto M, const uint8_t* a, const float* sa, const int32_t* rows, const uint8_t* w,
+                  const float* sw, int K, int NOUT, bf16_t* c) {
+    constexpr int MODE = decltype(M)::value;
+    constexpr bool gateup = MODE == MODE_GATEUP;
+    const int64_t ring_tiles =
+        G * cdiv64(max_rows, (int64_t)128 * G) * (NOUT / (gateup ? 128 : 256));
+    if (r192_ok(max_rows, G, K / 128, ring_tiles)) {
+      launch_r192_fp8(gateup, a, rows, goff, G, max_rows, w, K, NOUT, c, NOUT, num_cus(),
+                      r192_height(max_rows, G, NOUT / (gateup ? 128 : 256), 64), sa, sw, s);
+      return;
+    }
     const KSplit sp =
-        make_split(ring_splits(true, 128, max_rows, G, d / 128, ffn, pbytes), d / 128, P);
-    gemm_pass_f8<MODE_GATEUP>(x, rows_in, goff, G, max_rows, w_gate_up, d, ffn, H, ffn,
-                              x_scale, s_gate_up, s, sp);
-    reduce_split<MODE_GATEUP>(sp, rows_in, goff, G, max_rows, ffn, H, ffn, s);
-  }
+        make_split(ring_splits(gateup, 128, max_rows, G, K / 128, NOUT, pbytes), K / 128, P);
+    gemm_pass_f8<MODE>(a, rows, goff, G, max_rows, w, K, NOUT, c, NOUT, sa, sw, s, sp);
+    reduce_split<MODE>(sp, rows, goff, G, max_rows, NOUT, c, NOUT, s);
+  };
+  if (profile) prof_begin(prof_gate_up, s);
+  pass(std::integral_constant<int, MODE_GATEUP>{}, x, x_scale, rows_in, w_gate_up, s_gate_up, d, ffn, H);
   if (profile) prof_end(prof_gate_up, s);
   if (profile) prof_begin(prof_gate_up + 1, s);
   hipError_t e = launch_quantize_fp8(1, H, max_rows, ffn, goff ? goff + G : nullptr, Hq, Hs, s);
   if (e != hipSuccess) return e;
-  {
-    const KSplit sp = make_split(ring_splits(false, 128, max_rows, G, ffn / 128, d, pbytes),
-                                 ffn / 128, P);
-    gemm_pass_f8<MODE_DOWN>(Hq, rows_out, goff, G, max_rows, w_down, ffn, d, Y, d, Hs, s_down,
-                            s, sp);
-    reduce_split<MODE_DOWN>(sp, rows_out, goff, G, max_rows, d, Y, d, s);
-  }
+  pass(std::integral_constant<int, MODE_DOWN>{}, Hq, Hs, rows_out, w_down, s_down, ffn, d, Y);
   if (profile) prof_end(prof_gate_up + 1, s);
   return hipGetLastError();
 }
@@ -1633,7 +1637,7 @@ hipError_t launch_dense_linear(int dtype, int m, int n, int kdim, const void* a,
   const int64_t ring_tiles = cdiv64(m, 128) * (n / (n % 256 == 0 ? 256 : 128));
   if (dtype != 1 || (ring_tiles < num_cus() && kdim < 4096))
     launch_gemm_r64(dtype, false, a, nullptr, nullptr, 1, m, w, kdim, n, out, n, num_cus(), s);
-  else if (n % 256 == 0 && r192_ok(m, 1, kdim, ring_tiles))
+  else if (n % 256 == 0 && r192_ok(m, 1, kdim / 64, ring_tiles))
     launch_r192_down(a, nullptr, nullptr, 1, m, w, kdim, n, out, n, num_cus(),
                      r192_height(m, 1, n / 256), s);
   else

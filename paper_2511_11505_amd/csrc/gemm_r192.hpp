@@ -28,11 +28,17 @@
 //            the way into LDS: a lane holds eight consecutive output columns
 //            and stores them as they are, without staging.
 //
+//   FP8      E4M3 codes on v_mfma_scale_f32_32x32x64_f8f6f4 (unit scales): the
+//            same bytes per block, 32-row fragments, heights in steps of 64;
+//            the epilogue applies the row and column scales, which copies
+//            into LDS bring at the tile's start.
+//
 // Measured (us, ring -> this): 8192 rows, d 5120, F 8192, dense gate/up 1228
 // -> 998 (1.38 PFLOP/s, as fast as the vendor library's dense kernel), down
-// 590 -> 546; 16 groups of about 512 rows of the same: 1410 -> 1307 and 706
-// -> 673; 32 groups of 1024 rows, d 7168, F 2048: 1755 -> 1670 and 978 ->
-// 829; 64 groups of 384 rows, d 2048, F 1408: 347 -> 300 and 199 -> 178.
+// 590 -> 546; 16 groups of about 512 rows of the same: 1410 -> 1290 and 706
+// -> 641; 32 groups of 1024 rows, d 7168, F 2048: 1755 -> 1690 and 978 ->
+// 829, FP8 916 -> 860 and 565 -> 470; 64 groups of 384 rows, d 2048, F 1408:
+// 347 -> 298 and 199 -> 176.
 #pragma once
 
 #include <algorithm>
@@ -80,29 +86,41 @@ __device__ __forceinline__ void dma4_at(const void* g, unsigned lds) {
                : "memory");
 }
 
-typedef __attribute__((address_space(3))) bf16x8 lds_frag_t;
+typedef __attribute__((address_space(3))) bf16x8 lds_bf16x8_t;
+typedef int int32x4 __attribute__((ext_vector_type(4)));
+typedef int int32x8 __attribute__((ext_vector_type(8)));
+typedef __attribute__((address_space(3))) int32x4 lds_int32x4_t;
 
-template <int MODE>
+template <int MODE, bool F8>
 __global__ __launch_bounds__(256, 1) void gemm_r192_kernel(
-    const bf16_t* __restrict__ A, const int32_t* __restrict__ rows,
-    const int32_t* __restrict__ goff, int G, int64_t m_total, const bf16_t* __restrict__ B, int K,
-    int NOUT, bf16_t* __restrict__ C, int ldc, int hmax) {
+    const typename std::conditional<F8, uint8_t, bf16_t>::type* __restrict__ A,
+    const int32_t* __restrict__ rows, const int32_t* __restrict__ goff, int G, int64_t m_total,
+    const typename std::conditional<F8, uint8_t, bf16_t>::type* __restrict__ B, int K, int NOUT,
+    bf16_t* __restrict__ C, int ldc, int hmax, const float* __restrict__ sA,
+    const float* __restrict__ sB) {
+  using TE = typename std::conditional<F8, uint8_t, bf16_t>::type;
+  using FragT = typename std::conditional<F8, int32x8, bf16x8>::type;
+  using AccT = typename std::conditional<F8, floatx16, floatx4>::type;
+  constexpr int ES = sizeof(TE), CE = 16 / ES;     // bytes, elements per 16-byte chunk
   constexpr int NT = 256, BM = 192, BN = 256;
-  constexpr int ROWB = 128;                        // staged bytes per row and K block (64 bf16)
-  constexpr int BK = 64;
+  constexpr int ROWB = 128, BK = ROWB / ES;        // staged bytes per row and K block
+  constexpr int FR = F8 ? 32 : 16;                 // fragment rows
+  constexpr int HU = 2 * FR;                       // tile heights: multiples of this
   constexpr int ASTAGE = BM * ROWB, BSTAGE = BN * ROWB;   // two A slots, three B slots
   constexpr int NCOL = MODE == MODE_GATEUP ? BN / 2 : BN;
-  constexpr int TN = 8, TMAX = BM / 32, B_LD = 8;
+  constexpr int TN = 128 / FR, B_LD = 8, A_MAX = BM / 32; // B fragments, DMAs per wave
+  constexpr int TMIN = 128 / HU;                   // shorter tiles take this loop
   __shared__ int s_goff[kMaxGroups + 1];
   __shared__ int s_tpre[kMaxGroups + 1];
   __shared__ int s_wtot[NT / 64];
   __shared__ __align__(16) int s_rows[NT];         // row indices of a tile
+  __shared__ __align__(16) float s_sa[F8 ? NT : 4], s_sb[F8 ? NT : 4];   // its scales
   __shared__ __align__(1024) unsigned char ring[2 * ASTAGE + 3 * BSTAGE];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
-  const int l16 = lane & 15, quad = lane >> 4;
+  const int lr = lane & (FR - 1), lh = lane / FR;  // fragment row, K part (and column part)
   auto uni = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
   sched_setup<NT>(goff, G, m_total, s_goff, s_tpre, s_wtot, hmax);
   const int nn = NOUT / NCOL;
@@ -111,31 +129,39 @@ __global__ __launch_bounds__(256, 1) void gemm_r192_kernel(
   const int64_t xcd_base = (int64_t)(blockIdx.x % kXcd) * per_xcd;
   const int64_t stride = gridDim.x / kXcd;
   const size_t bstride = (size_t)(MODE == MODE_GATEUP ? 2 * NOUT : NOUT) * K;
-  const int KT = K / BK;                           // even, at least 4
+  const int KT = K / BK;                           // at least 4
   // a DMA copies 8 rows of 128 bytes: lane l row l / 8, and the 16-byte chunk
   // that belongs at position l % 8 of that row (chunk c of row r sits at
-  // c ^ ((r / 2) % 8))
+  // c ^ ((r / 2) % 8), so that the lanes an LDS read serves together cover
+  // every bank once)
   const int drow = lane >> 3, dpos = lane & 7;
   const unsigned ring_lds = lds_addr(ring);
+  const unsigned ldsA = ring_lds + wave * 1024;
   const unsigned ldsB = ring_lds + 2 * ASTAGE + wave * (B_LD * 1024);
 
-  // this lane's 16 bytes of a fragment row in each half block, from the
+  // LDS address of this lane's bytes of a fragment row in each half block
+  // (16 bytes for bf16; for FP8 32, the second 16 at position ^ 1), from the
   // wave's first A and B fragment
-  const int sw = (l16 >> 1) & 7;
-  unsigned ab[2], bb[2];                           // LDS byte addresses
+  const int sw = (lr >> 1) & 7;
+  unsigned ab[2], bb[2];
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks) {
-    const int fo = l16 * ROWB + (((ks * 4 + quad) ^ sw) << 4);
-    ab[ks] = ring_lds + wm * 16 * ROWB + fo;
+    const int fo = lr * ROWB + (((ks * 4 + (F8 ? 2 * lh : lh)) ^ sw) << 4);
+    ab[ks] = ring_lds + wm * FR * ROWB + fo;
     bb[ks] = ring_lds + 2 * ASTAGE + wn * (MODE == MODE_GATEUP ? 64 : 128) * ROWB + fo;
   }
-  // B DMA i of this wave fills tile rows 64 wave + 8 i ..: of each 32 rows,
-  // row 16 t + 4 q + v holds output column 8 q + 4 t + v
+  // B DMA i of this wave fills tile rows 64 wave + 8 i ..; row r of each 32
+  // holds the output column that puts consecutive columns into a lane's
+  // accumulators: bf16 row 16 t + 4 q + v column 8 q + 4 t + v, FP8 row
+  // 8 a + 4 h + b column 16 h + 4 a + b
   unsigned bl[B_LD];
 #pragma unroll
-  for (int i = 0; i < B_LD; ++i)
-    bl[i] = (unsigned)(((i >> 2) * 32 + (i & 1) * 16 + ((i >> 1) & 1) * 4 + (drow >> 2) * 8 +
-                        (drow & 3)) * K * 2 + (dpos ^ ((i & 1) * 4 + (drow >> 1))) * 16);
+  for (int i = 0; i < B_LD; ++i) {
+    const int r = (i & 3) * 8 + drow;
+    const int col = F8 ? 16 * ((r >> 2) & 1) + 4 * (r >> 3) + (r & 3)
+                       : 8 * ((r & 15) >> 2) + 4 * (r >> 4) + (r & 3);
+    bl[i] = (unsigned)(((i >> 2) * 32 + col) * K * ES + (dpos ^ ((r >> 1) & 7)) * 16);
+  }
 
   struct Item {
     int g, m0, n0, row_base, rows_t, tma;
@@ -156,28 +182,37 @@ __global__ __launch_bounds__(256, 1) void gemm_r192_kernel(
     it.n0 = nt * NCOL;
     it.row_base = uni(s_goff[it.g]);
     const int rows_g = uni(s_goff[it.g + 1]) - it.row_base;
-    // the group's tiles have equal heights, a multiple of 32 rows
-    const int h = uni(((rows_g + Tg - 1) / Tg + 31) & ~31);
+    // the group's tiles have equal heights, a multiple of HU rows
+    const int h = uni((rows_g + Tg - 1) / Tg + HU - 1) & ~(HU - 1);
     it.m0 = mt * h;
     it.rows_t = min(rows_g - it.m0, h);
-    it.tma = max(4, (it.rows_t + 31) / 32);
+    it.tma = max(TMIN, (it.rows_t + HU - 1) / HU);
   };
   // row indices of an item's rows into s_rows (rows past its end: the last)
   auto fetch_rows = [&](const Item& it) {
     dma4_at(rows + it.row_base + it.m0 + min(wave * 64 + lane, it.rows_t - 1),
             lds_addr(s_rows) + wave * 256);
   };
-  // the copies' sources: the next block of this wave's A rows (tma DMAs) and
-  // B rows
-  const bf16_t* pa[TMAX];
+  // FP8: the scales of an item's rows (gate/up: its row indices are still in
+  // s_rows) and weight rows, the latter in the order of the B tile's columns
+  auto fetch_scales = [&](const Item& it) {
+    int r = min(wave * 64 + lane, it.rows_t - 1);
+    r = (MODE == MODE_GATEUP && rows) ? s_rows[r] : it.row_base + it.m0 + r;
+    dma4_at(sA + r, lds_addr(s_sa) + wave * 256);
+    const int c = wave * 64 + lane;
+    const float* sg = sB + (size_t)it.g * (MODE == MODE_GATEUP ? 2 * NOUT : NOUT) + it.n0;
+    dma4_at(sg + (MODE == MODE_GATEUP && c >= 128 ? NOUT + c - 128 : c), lds_addr(s_sb) + wave * 256);
+  };
+  // the copies' sources: the next block of this wave's A rows (A DMA i fills
+  // tile rows 32 i + 8 wave ..) and B rows
+  const TE* pa[A_MAX];
   const unsigned char* pb = nullptr;
   auto sources_a = [&](const Item& it) {
 #pragma unroll
-    for (int i = 0; i < TMAX; ++i) {
-      const int blk = wave * it.tma + i;
-      const int r = min(blk * 8 + drow, it.rows_t - 1);
+    for (int i = 0; i < A_MAX; ++i) {
+      const int r = min((4 * i + wave) * 8 + drow, it.rows_t - 1);
       const int v = (MODE == MODE_GATEUP && rows) ? s_rows[r] : it.row_base + it.m0 + r;
-      pa[i] = A + (size_t)v * K + (dpos ^ (((blk & 1) * 4 + (drow >> 1)) & 7)) * 8;
+      pa[i] = A + (size_t)v * K + (dpos ^ ((wave & 1) * 4 + (drow >> 1))) * CE;
     }
   };
   auto source_b = [&](const Item& it) {
@@ -198,14 +233,13 @@ __global__ __launch_bounds__(256, 1) void gemm_r192_kernel(
   }
   sources_a(it);
   source_b(it);
-  unsigned ldsA = ring_lds + wave * it.tma * 1024;
-  // LDS offsets of the B slots of the current block, the next and the one
-  // after
-  unsigned ob0 = 0, ob1 = BSTAGE, ob2 = 2 * BSTAGE;
-  auto copy_a = [&](auto S) __attribute__((always_inline)) {
-    static_for<TMAX>([&](auto I) __attribute__((always_inline)) {
+  // LDS offsets of the slots of the current block, the next (and, B, the one
+  // after)
+  unsigned oa0 = 0, oa1 = ASTAGE, ob0 = 0, ob1 = BSTAGE, ob2 = 2 * BSTAGE;
+  auto copy_a = [&](unsigned oa) __attribute__((always_inline)) {
+    static_for<A_MAX>([&](auto I) __attribute__((always_inline)) {
       constexpr int i = decltype(I)::value;
-      if (i < it.tma) dma16_o<decltype(S)::value * ASTAGE + i * 1024>(pa[i], ldsA);
+      dma16_o<i * 4096>(pa[i], ldsA + oa);
       pa[i] += BK;
     });
   };
@@ -216,182 +250,236 @@ __global__ __launch_bounds__(256, 1) void gemm_r192_kernel(
     });
     pb += ROWB;
   };
-  copy_a(std::integral_constant<int, 0>{});
+  copy_a(oa0);
   copy_b(ob0);
   copy_b(ob1);
-  copy_a(std::integral_constant<int, 1>{});
+  copy_a(oa1);
   copy_b(ob2);
 
   for (;;) {
     const bool has_next = j + stride < per_xcd && xcd_base + j + stride < total;
+    // without a next item the copies past this one's end re-read its own rows
+    itN = it;
     if (has_next) decode(xcd_base + j + stride, itN);
     auto tile = [&](auto TMA) __attribute__((always_inline)) {
       constexpr int TM = decltype(TMA)::value;
+      constexpr int A_LD = TM * (HU / 32);
       constexpr int MPS = TM * TN, NR = TM + TN;
-      floatx4 acc[TM][TN];
+      AccT acc[TM][TN];
       static_for<TM * TN>([&](auto q) __attribute__((always_inline)) {
-        acc[q / TN][q % TN] = floatx4{0.f, 0.f, 0.f, 0.f};
+        if constexpr (F8)
+          acc[q / TN][q % TN] = AccT{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f,
+                                     0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        else
+          acc[q / TN][q % TN] = AccT{0.f, 0.f, 0.f, 0.f};
       });
-      bf16x8 F[2][TM + TN];
+      FragT F[2][TM + TN];
       // fragment r of the half block at LDS addresses la (A) and lb (B), in
-      // the order the MFMAs use them: A0, B0 .. B7, A1 ..
-      auto read1 = [&](bf16x8 (&f)[TM + TN], unsigned la, unsigned lb, auto R)
-          __attribute__((always_inline)) {
+      // the order the MFMAs use them: A0, all B, A1 ..  (FP8: la2 / lb2 are
+      // the addresses of the lane's second 16 bytes)
+      auto read1 = [&](FragT (&f)[TM + TN], unsigned la, unsigned lb, unsigned la2, unsigned lb2,
+                       auto R) __attribute__((always_inline)) {
         constexpr int r = decltype(R)::value;
         constexpr int x = r == 0 ? 0 : (r <= TN ? TM + r - 1 : r - TN);
         constexpr int n = x - TM;
-        if constexpr (x < TM)
-          f[x] = *(const lds_frag_t*)(uintptr_t)(la + x * 32 * ROWB);
-        else
-          f[x] = *(const lds_frag_t*)(uintptr_t)(
-              lb + (MODE == MODE_GATEUP ? (n & 3) * 16 + (n >> 2) * 128 : n * 16) * ROWB);
+        constexpr int off = x < TM ? x * HU * ROWB
+                            : MODE == MODE_GATEUP
+                                ? ((n % (TN / 2)) * FR + (n / (TN / 2)) * 128) * ROWB
+                                : n * FR * ROWB;
+        const unsigned p = (x < TM ? la : lb) + off;
+        if constexpr (F8) {
+          const int32x4 lo = *(const lds_int32x4_t*)(uintptr_t)p;
+          const int32x4 hi = *(const lds_int32x4_t*)(uintptr_t)((x < TM ? la2 : lb2) + off);
+          f[x] = int32x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        } else {
+          f[x] = *(const lds_bf16x8_t*)(uintptr_t)p;
+        }
       };
-      using I0 = std::integral_constant<int, 0>;
-      using I1 = std::integral_constant<int, 1>;
-      // block 0 has landed in every wave (after it, at least 20 copies)
-      wait_vmcnt<20>();
+      // block 0 has landed in every wave (after it, B 1, A 1, B 2)
+      wait_vmcnt<A_MAX + 2 * B_LD>();
       barrier_nofence();
+      if constexpr (F8) fetch_scales(it);
       // gate/up: the next tile's row indices; down: this tile's
-      if (rows && (MODE == MODE_DOWN || has_next)) fetch_rows(MODE == MODE_DOWN ? it : itN);
-      static_for<NR>([&](auto r) __attribute__((always_inline)) { read1(F[0], ab[0], bb[0] + ob0, r); });
-      // Half block KS of a block (A slot S): its MFMAs on fc, the reads of the
-      // next half block into fn between them.  In the second half the
-      // workgroup meets after the first MFMA: the next block has landed (only
-      // the B copies of the block after it may be in flight), and every wave
-      // holds this half in registers, so the block's slots are free.  The A
-      // copies of the block two ahead and the B copies of the block three
-      // ahead go out there.  WHEN: 0 all of them are this item's, 1 the
-      // second block's B copies are the next item's (the item's last four
-      // blocks begin), 2 all are the next item's.
-      auto half = [&](bf16x8 (&fc)[TM + TN], bf16x8 (&fn)[TM + TN], int tmaN, auto S, auto KS,
-                      auto WHEN) __attribute__((always_inline)) {
-        constexpr int slot = decltype(S)::value, ks = decltype(KS)::value;
-        constexpr int when = decltype(WHEN)::value;
-        constexpr bool last = when == 2;
-        constexpr bool end = last && slot == 1 && ks == 1;
-        constexpr bool nextb = last || (when == 1 && slot == 1);
+      if (rows) fetch_rows(MODE == MODE_DOWN ? it : itN);
+      {
+        const unsigned la = ab[0] + oa0, lb = bb[0] + ob0;
+        static_for<NR>([&](auto r) __attribute__((always_inline)) {
+          read1(F[0], la, lb, la ^ 16, lb ^ 16, r);
+        });
+      }
+      // Half block KS of a block: its MFMAs on fc, the reads of the next half
+      // block into fn between them.  In the second half the workgroup meets
+      // after the first MFMA: the next block has landed (only the B copies
+      // of the block after it may be in flight), and every wave holds this
+      // half in registers, so the block's slots are free.  The A copies of
+      // the block two ahead and the B copies of the block three ahead go out
+      // there.  WHEN: 0 all of them are this item's, 1 the B copies are the
+      // next item's (the item's third last block), 2 all are (its second
+      // last), 3 so in its last block.
+      auto half = [&](FragT (&fc)[TM + TN], FragT (&fn)[TM + TN], auto KS, auto WHEN)
+          __attribute__((always_inline)) {
+        constexpr int ks = decltype(KS)::value, when = decltype(WHEN)::value;
+        constexpr bool end = when == 3 && ks == 1;
         // the next half block's fragments; opaque, so that their addresses
-        // stay two registers and immediate offsets
-        unsigned la = ab[ks ^ 1] + (ks == 0 ? slot : slot ^ 1) * ASTAGE;
+        // stay a few registers and immediate offsets
+        unsigned la = ab[ks ^ 1] + (ks == 0 ? oa0 : oa1);
         unsigned lb = bb[ks ^ 1] + (ks == 0 ? ob0 : ob1);
         asm volatile("" : "+v"(la), "+v"(lb));
+        unsigned la2 = la ^ 16, lb2 = lb ^ 16;
+        if constexpr (F8) asm volatile("" : "+v"(la2), "+v"(lb2));
         static_for<MPS>([&](auto Q) __attribute__((always_inline)) {
           constexpr int q = decltype(Q)::value;
           constexpr int i = q / TN, n = q % TN;
-          acc[i][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fc[TM + n], fc[i], acc[i][n], 0, 0, 0);
+          if constexpr (F8)
+            acc[i][n] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fc[TM + n], fc[i], acc[i][n],
+                                                                        0, 0, 0, 127, 0, 127);
+          else
+            acc[i][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fc[TM + n], fc[i], acc[i][n], 0, 0, 0);
           __builtin_amdgcn_sched_barrier(0);
           if constexpr (q == 0 && ks == 1) {
             wait_lgkm0();
-            if constexpr (!end) {
-              if (!last || has_next)
-                wait_vmcnt<B_LD>();
-              else
-                wait_vmcnt<0>();
-            }
+            if constexpr (!end) wait_vmcnt<B_LD>();
             barrier_nofence();
             __builtin_amdgcn_sched_barrier(0);
           }
           if constexpr (!end)
             static_for<NR>([&](auto R) __attribute__((always_inline)) {
-              if constexpr (q == 1 + decltype(R)::value * (MPS * 3 / 4) / NR) read1(fn, la, lb, R);
+              constexpr int at = F8 ? decltype(R)::value * MPS * 3 / 4 / NR
+                                    : 1 + decltype(R)::value * (MPS * 3 / 4) / NR;
+              if constexpr (q == at) read1(fn, la, lb, la2, lb2, R);
             });
           if constexpr (ks == 1)
-            static_for<TMAX + B_LD>([&](auto D) __attribute__((always_inline)) {
+            static_for<A_MAX + B_LD>([&](auto D) __attribute__((always_inline)) {
               constexpr int d = decltype(D)::value;
-              if constexpr (q == 1 + d * (MPS - 2) / (TMAX + B_LD)) {
-                if constexpr (d < TMAX) {
-                  if constexpr (!last) {
-                    if constexpr (d < TM) dma16_o<slot * ASTAGE + d * 1024>(pa[d], ldsA);
-                  } else {
-                    if (d < tmaN) dma16_o<slot * ASTAGE + d * 1024>(pa[d], ldsA);
+              constexpr int at = F8 ? d * (MPS - 1) / (A_MAX + B_LD) : 1 + d * (MPS - 2) / (A_MAX + B_LD);
+              if constexpr (q == at) {
+                if constexpr (d < A_MAX) {
+                  if constexpr (when >= 2 || d < A_LD) {
+                    dma16_o<d * 4096>(pa[d], ldsA + oa0);
+                    pa[d] += BK;
                   }
-                  pa[d] += BK;
                 } else {
-                  if (!nextb || has_next)
-                    dma16_so<(d - TMAX) * 1024>(pb, bl[d - TMAX], ldsB + ob0);
-                  if constexpr (d == TMAX + B_LD - 1) pb += ROWB;
+                  dma16_so<(d - A_MAX) * 1024>(pb, bl[d - A_MAX], ldsB + ob0);
+                  if constexpr (d == A_MAX + B_LD - 1) pb += ROWB;
                 }
               }
             });
           __builtin_amdgcn_sched_barrier(0);
         });
         if constexpr (ks == 1) {
-          const unsigned o = ob0;
+          const unsigned o = ob0, p = oa0;
           ob0 = ob1;
           ob1 = ob2;
           ob2 = o;
+          oa0 = oa1;
+          oa1 = p;
         }
       };
-      using W0 = std::integral_constant<int, 0>;
-      using W1 = std::integral_constant<int, 1>;
-      using W2 = std::integral_constant<int, 2>;
-      for (int kt = 0; kt + 4 < KT; kt += 2) {
-        half(F[0], F[1], 0, I0{}, I0{}, W0{});
-        half(F[1], F[0], 0, I0{}, I1{}, W0{});
-        half(F[0], F[1], 0, I1{}, I0{}, W0{});
-        half(F[1], F[0], 0, I1{}, I1{}, W0{});
+      using I0 = std::integral_constant<int, 0>;
+      using I1 = std::integral_constant<int, 1>;
+      using I2 = std::integral_constant<int, 2>;
+      using I3 = std::integral_constant<int, 3>;
+      for (int kt = 0; kt + 3 < KT; ++kt) {
+        half(F[0], F[1], I0{}, I0{});
+        half(F[1], F[0], I1{}, I0{});
       }
-      half(F[0], F[1], 0, I0{}, I0{}, W1{});
-      half(F[1], F[0], 0, I0{}, I1{}, W1{});
-      if (has_next) source_b(itN);
-      half(F[0], F[1], 0, I1{}, I0{}, W1{});
-      half(F[1], F[0], 0, I1{}, I1{}, W1{});
-      // (none of the A copies without a next item: tmaN 0; its row indices
-      // landed by the meeting in this item's second block)
-      int tmaN = 0;
-      if (has_next) {
-        sources_a(itN);
-        tmaN = itN.tma;
-        ldsA = ring_lds + wave * tmaN * 1024;
-      }
-      half(F[0], F[1], tmaN, I0{}, I0{}, W2{});
-      half(F[1], F[0], tmaN, I0{}, I1{}, W2{});
-      half(F[0], F[1], tmaN, I1{}, I0{}, W2{});
-      half(F[1], F[0], tmaN, I1{}, I1{}, W2{});
-      // (this tile's row indices landed by its second block)
-      // epilogue: element v of fragments 2p, 2p + 1 is column 8 quad + v (+ 4)
-      // of the wave's p-th 32 columns, row l16 of the fragment
+      source_b(itN);
+      half(F[0], F[1], I0{}, I1{});
+      half(F[1], F[0], I1{}, I1{});
+      // (the next item's row indices landed by the meeting in this item's
+      // second block; its copies fill every row block, whatever its height)
+      sources_a(itN);
+      half(F[0], F[1], I0{}, I2{});
+      half(F[1], F[0], I1{}, I2{});
+      half(F[0], F[1], I0{}, I3{});
+      half(F[1], F[0], I1{}, I3{});
+      // a use of every accumulator here: else the compiler sinks the FP8 MFMAs
+      // of the last blocks into the epilogue's branches, past the copies
+      if constexpr (F8)
+        static_for<TM * TN>([&](auto q) __attribute__((always_inline)) {
+          const AccT& x = acc[q / TN][q % TN];
+          asm volatile("" : : "a"(x));
+        });
+      // (this tile's row indices and scales landed by its second block)
+      // epilogue: a lane's columns are consecutive (bf16: element v of
+      // fragments 2p, 2p + 1 is column 8 lh + v (+ 4) of the wave's p-th 32;
+      // FP8: element v of fragment p column 16 lh + v), of row lr of the
+      // fragment
       static_for<TM>([&](auto I) __attribute__((always_inline)) {
         constexpr int i = decltype(I)::value;
-        const int m = i * 32 + wm * 16 + l16;
+        const int m = i * HU + wm * FR + lr;
         if (m < it.rows_t) {
           int64_t orow = it.row_base + it.m0 + m;
           if (MODE == MODE_DOWN && rows) orow = s_rows[m];
-          bf16_t* p = C + orow * ldc + it.n0 + wn * (MODE == MODE_GATEUP ? 64 : 128) + 8 * quad;
+          const int wc = wn * (MODE == MODE_GATEUP ? 64 : 128);
+          bf16_t* p = C + orow * ldc + it.n0 + wc + (F8 ? 16 : 8) * lh;
+          const float sa = F8 ? s_sa[m] : 1.f;
           static_for<(MODE == MODE_GATEUP ? 2 : 4)>([&](auto P) __attribute__((always_inline)) {
             constexpr int n = decltype(P)::value;
-            Vec16<bf16_t> o;
+            if constexpr (F8) {
+              // (opaque, and a scheduling barrier after each store: else every
+              // column scale is read at once, into more registers than there are)
+              unsigned sbo = wc + 32 * n + 16 * lh;
+              asm volatile("" : "+v"(sbo));
+              const float* sb = s_sb + sbo;
+              static_for<2>([&](auto S) __attribute__((always_inline)) {
+                constexpr int s0 = decltype(S)::value * 8;
+                Vec16<bf16_t> o;
 #pragma unroll
-            for (int v = 0; v < 8; ++v) {
-              const float x = acc[i][2 * n + (v >> 2)][v & 3];
-              if constexpr (MODE == MODE_GATEUP)
-                o.set(v, swiglu_bf16_epi(x, acc[i][4 + 2 * n + (v >> 2)][v & 3]));
-              else
-                o.set(v, x);
+                for (int v = 0; v < 8; ++v) {
+                  const float x = acc[i][n][s0 + v] * sa * sb[s0 + v];
+                  if constexpr (MODE == MODE_GATEUP)
+                    o.set(v, swiglu_bf16_epi(x, acc[i][2 + n][s0 + v] * sa * sb[128 + s0 + v]));
+                  else
+                    o.set(v, x);
+                }
+                st16(p + 32 * n + s0, o.raw);
+                __builtin_amdgcn_sched_barrier(0);
+              });
+            } else {
+              Vec16<bf16_t> o;
+#pragma unroll
+              for (int v = 0; v < 8; ++v) {
+                const float x = acc[i][2 * n + (v >> 2)][v & 3];
+                if constexpr (MODE == MODE_GATEUP)
+                  o.set(v, swiglu_bf16_epi(x, acc[i][4 + 2 * n + (v >> 2)][v & 3]));
+                else
+                  o.set(v, x);
+              }
+              st16(p + 32 * n, o.raw);
             }
-            st16(p + 32 * n, o.raw);
           });
         }
       });
     };
-    switch (it.tma) {
-      case 4: tile(std::integral_constant<int, 4>{}); break;
-      case 5: tile(std::integral_constant<int, 5>{}); break;
-      default: tile(std::integral_constant<int, 6>{}); break;
+    if constexpr (F8) {
+      if (it.tma == 2)
+        tile(std::integral_constant<int, 2>{});
+      else
+        tile(std::integral_constant<int, 3>{});
+    } else {
+      switch (it.tma) {
+        case 4: tile(std::integral_constant<int, 4>{}); break;
+        case 5: tile(std::integral_constant<int, 5>{}); break;
+        default: tile(std::integral_constant<int, 6>{}); break;
+      }
     }
     if (!has_next) break;
     j += stride;
     it = itN;
   }
+  wait_vmcnt<0>();   // no copy outlives the workgroup's LDS
 }
 
-template <int MODE>
+template <int MODE, bool F8>
 void run_r192(const void* A, const int32_t* rows, const int32_t* goff, int G, int64_t m_total,
-              const void* B, int K, int NOUT, void* C, int ldc, int cus, int hmax, hipStream_t s) {
+              const void* B, int K, int NOUT, void* C, int ldc, int cus, int hmax, const float* sA,
+              const float* sB, hipStream_t s) {
+  using TE = typename std::conditional<F8, uint8_t, bf16_t>::type;
   const int64_t tiles = (cdiv64(m_total, hmax) + G) * (NOUT / (MODE == MODE_GATEUP ? 128 : 256));
   const int64_t grid = std::min<int64_t>(cdiv64(tiles, kXcd), cdiv64(cus, kXcd)) * kXcd;
-  launch_k(gemm_r192_kernel<MODE>, (unsigned)grid, 256, 0, s, (const bf16_t*)A, rows, goff, G,
-           m_total, (const bf16_t*)B, K, NOUT, (bf16_t*)C, ldc, hmax);
+  launch_k(gemm_r192_kernel<MODE, F8>, (unsigned)grid, 256, 0, s, (const TE*)A, rows, goff, G,
+           m_total, (const TE*)B, K, NOUT, (bf16_t*)C, ldc, hmax, sA, sB);
 }
 
 }  // namespace

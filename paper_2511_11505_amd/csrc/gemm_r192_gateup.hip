@@ -1,5 +1,5 @@
-// The gate/up pass of gemm_r192.hpp (a file of its own: each takes about a minute
-// to compile).
+// The bf16 gate/up pass of gemm_r192.hpp (a file of its own: each takes about a
+// minute to compile).
 #include "gemm_r192.hpp"
 
 namespace fs {
@@ -7,7 +7,7 @@ namespace fs {
 void launch_r192_gateup(const void* A, const int32_t* rows, const int32_t* goff, int G,
                     int64_t m_total, const void* B, int K, int NOUT, void* C, int ldc, int cus,
                     int hmax, hipStream_t s) {
-  run_r192<MODE_GATEUP>(A, rows, goff, G, m_total, B, K, NOUT, C, ldc, cus, hmax, s);
+  run_r192<MODE_GATEUP, false>(A, rows, goff, G, m_total, B, K, NOUT, C, ldc, cus, hmax, nullptr, nullptr, s);
 }
 
 }  // namespace fs

@@ -11,6 +11,7 @@ import torch
 
 import oracle
 from paper_2511_11505_amd import _lib as L
+from paper_2511_11505_amd.block import fragment_ordered_fp8
 from tests._util import TOL, f64, rel_err
 from workloads import CONFIGS
 
@@ -119,3 +120,42 @@ def test_dense_linear_edges(dtype, m, n, kd):
     L.fs_dense_linear(L.FS_F32 if dtype == "f32" else L.FS_BF16, m, n, kd, a, w, out)
     torch.cuda.synchronize()
     assert rel_err(out, oracle.dense_linear(f64(a), f64(w))) <= TOL[dtype]
+
+
+# FP8 on the 192-row tiles (heights 128 and 192, odd and even K block counts)
+# against the fragment-ordered kernel on the same codes: H is the same bits;
+# the down pass's fp32 sums may round differently in the last place, so an
+# output differs by one bf16 step at most (2^-7 of its value), or, where the
+# sum cancels, by the fp32 rounding of its terms (2048 2^-24 of the rms bounds
+# it: 1.3e-4).
+@pytest.mark.parametrize("counts,d,F,gather", [(TALL, 2048, 1408, True), (TALL * 2, 512, 2816, False),
+                                               ([2050], 768, 2048, False), ([3000, 1], 1280, 1408, True)])
+def test_ffn_fp8_tall_tiles(counts, d, F, gather):
+    X, rows, goff, wgu, wd, n_src = ffn_case("bf16", counts, d, F, gather, seed=9)
+    G, M = len(counts), int(goff[-1])
+
+    def quant(t):
+        c = torch.empty(t.shape, dtype=torch.uint8, device=DEV)
+        s = torch.empty(t.shape[:-1], dtype=torch.float32, device=DEV)
+        L.fs_quantize_fp8(L.FS_BF16, s.numel(), t.shape[-1], t, c, s)
+        return c, s
+
+    (xc, xs), (gc, gs), (dc, ds) = quant(X), quant(wgu), quant(wd)
+    desc = L.make_desc(CONFIGS["tiny"].scaled(hidden=d, ffn=F, dtype="bf16"))
+    ws = torch.empty((L.fs_workspace_size(desc, L.FS_OP_GROUPED_FFN_FP8, M, F),), dtype=torch.uint8,
+                     device=DEV)
+    go = torch.from_numpy(goff).to(DEV)
+    out, ref = (torch.full((n_src, d), float("nan"), device=DEV).to(torch.bfloat16) for _ in range(2))
+    H = lambda: ws[:2 * M * F].clone()
+    L.fs_grouped_expert_ffn_fp8(desc, G, F, xc, xs, rows, go, M, gc, gs, dc, ds, out, ws)
+    h_out = H()
+    L.fs_grouped_expert_ffn_fp8_fo(desc, G, F, xc, xs, rows, go, M, fragment_ordered_fp8(gc), gs,
+                                   fragment_ordered_fp8(dc), ds, ref, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(h_out, H())
+    at = rows.long() if gather else torch.arange(M, device=DEV)
+    o, r = out[at].double(), ref[at].double()
+    assert torch.all((o - r).abs() <= 2.0 ** -7 * r.abs() + 1.3e-4 * r.square().mean().sqrt())
+    rest = torch.ones(n_src, dtype=torch.bool, device=DEV)
+    rest[at] = False
+    assert out[rest].isnan().all()
