@@ -314,15 +314,14 @@ static fs_status router_impl(const fs_moe_desc* d, const void* x, const void* w_
   int n_partials = 0;
   float* lout = logits_out;
   if (!logits_in) {
-    Carve c{reinterpret_cast<char*>(ws)};
-    float* scratch_logits = reinterpret_cast<float*>(c.take((size_t)N * E * sizeof(float)));
+    // ws holds the slice sums, or the logits of an unsplit router whose caller
+    // keeps none; never both, and both fit in router_ws_bytes from offset 0
     const bool split = fs::router_split(d->dtype, N, D, E);
-    float* dst;
+    float* dst = reinterpret_cast<float*>(ws);
     if (split) {
-      dst = reinterpret_cast<float*>(c.take((size_t)fs::router_slices(D) * N * E * sizeof(float)));
       n_partials = fs::router_slices(D);
     } else {
-      dst = logits_out ? logits_out : scratch_logits;
+      if (logits_out) dst = logits_out;
       lout = nullptr;  // already written by the router kernel
     }
     fs::prof_begin(FS_K_ROUTER, s);
