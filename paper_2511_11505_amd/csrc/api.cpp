@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -572,9 +573,14 @@ fs_status fs_grouped_expert_ffn_gathered(const fs_moe_desc* desc, int32_t n_grou
   if (ws_bytes < fs::ffn_ws_bytes(desc->dtype, max_rows, ffn, desc->hidden))
     return fail(FS_ERR_WORKSPACE, "workspace smaller than fs_workspace_size(FS_OP_GROUPED_FFN)");
   NEED(ws, "ws");
+  // max_rows is usually all N k slots, though n_groups of n_experts experts
+  // hold only their share of them (without offsets the one group holds max_rows)
+  int64_t likely = 0;
+  if (group_offsets)
+    likely = std::max<int64_t>(1, (int64_t)desc->n_tokens * desc->top_k * n_groups / desc->n_experts);
   FS_HIP(fs::launch_grouped_ffn(desc->dtype, n_groups, ffn, desc->hidden, x, gather_rows,
                                 nullptr, group_offsets, max_rows, w_gate_up, w_down, y, ws,
-                                S(stream), FS_K_GATE_UP),
+                                S(stream), FS_K_GATE_UP, likely),
          "grouped_ffn_gathered");
   return FS_OK;
 }

@@ -1336,8 +1336,12 @@ int r192_height(int64_t max_rows, int G, int n_tiles, int unit = 32) {
 // 384 rows 367 + 209 and 330 + 197.  32 groups of 1024 rows, d 7168, F 2048:
 // 1755 + 978 and 1690 + 829 (FP8 916 + 565 and 860 + 470).  One group of 8192 rows, gate/up of d 5120,
 // F 8192: 1228 -> 998 us (1.38 PFLOP/s).
-bool r192_ok(int64_t max_rows, int G, int k_blocks, int64_t ring_tiles) {
-  return max_rows >= (int64_t)112 * G && ring_tiles >= num_cus() && k_blocks >= 4;
+// rows are the likely ones where the bound is loose: 1300 replicated tokens, 160
+// experts top-6, 20 of them here, d 5120 (a bound of 390 rows a group, 49 of
+// them real): layer 452 us when the bound decides, 449 us so (441 to 446 us
+// before there were 192-row tiles); 2000 tokens 508 and 504 us.
+bool r192_ok(int64_t rows, int G, int k_blocks, int64_t ring_tiles) {
+  return rows >= (int64_t)112 * G && ring_tiles >= num_cus() && k_blocks >= 4;
 }
 
 // Kernel of one pass (gate/up: NOUT = F, K = d; down: NOUT = d, K = F).
@@ -1359,7 +1363,8 @@ enum PassKind { PASS_R64, PASS_STREAM, PASS_RING, PASS_R192 };
 // - unless the rows fit one tile and the weight tiles alone occupy enough CUs
 //   (more than a quarter): d 5120, F 8192, 64 rows: gate/up 60 -> 39 (256
 //   tiles), down 59 -> 43 (80 tiles).
-PassKind pass_kind(int dtype, bool gateup, int64_t max_rows, int G, int ffn, int d) {
+PassKind pass_kind(int dtype, bool gateup, int64_t max_rows, int64_t likely_rows, int G, int ffn,
+                   int d) {
   if (dtype != 1) return PASS_R64;
   const int NOUT = gateup ? ffn : d, K = gateup ? d : ffn;
   const bool stream = use_stream(dtype, max_rows, G, ffn, d);
@@ -1374,7 +1379,7 @@ PassKind pass_kind(int dtype, bool gateup, int64_t max_rows, int G, int ffn, int
   if (stream) return PASS_STREAM;
   if (ffn % 128 != 0 || d % 256 != 0) return PASS_R64;
   const int64_t ring_tiles = G * cdiv64(max_rows, (int64_t)128 * G) * (NOUT / (gateup ? 128 : 256));
-  return r192_ok(max_rows, G, K / 64, ring_tiles) ? PASS_R192 : PASS_RING;
+  return r192_ok(likely_rows, G, K / 64, ring_tiles) ? PASS_R192 : PASS_RING;
 }
 
 // One FP8 GEMM pass on 128 x 256 tiles, eight waves of 64 x 64 (as bf16:
@@ -1494,9 +1499,10 @@ hipError_t launch_grouped_ffn(int dtype, int G, int ffn, int d, const void* in,
                               const int32_t* rows_in, const int32_t* rows_out,
                               const int32_t* goff, int64_t max_rows,
                               const void* w_gate_up, const void* w_down, void* out, void* ws,
-                              hipStream_t s, int prof_gate_up) {
+                              hipStream_t s, int prof_gate_up, int64_t likely_rows) {
   const bool profile = prof_gate_up >= 0;
   if (max_rows <= 0) return hipSuccess;
+  if (likely_rows <= 0 || likely_rows > max_rows) likely_rows = max_rows;
   // H, then the fp32 partials of the passes that split K
   float* P = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) +
                                       ((size_t)max_rows * ffn * 2 + 255) / 256 * 256);
@@ -1504,7 +1510,7 @@ hipError_t launch_grouped_ffn(int dtype, int G, int ffn, int d, const void* in,
   auto pass = [&](auto M, const void* a, const int32_t* rows, const void* w, int K, int NOUT, void* c) {
     constexpr int MODE = decltype(M)::value;
     constexpr bool gateup = MODE == MODE_GATEUP;
-    const PassKind kind = pass_kind(dtype, gateup, max_rows, G, ffn, d);
+    const PassKind kind = pass_kind(dtype, gateup, max_rows, likely_rows, G, ffn, d);
     if (kind == PASS_R64) {
       launch_gemm_r64(dtype, gateup, a, rows, goff, G, max_rows, w, K, NOUT, c, NOUT, num_cus(), s);
     } else if (kind == PASS_R192) {

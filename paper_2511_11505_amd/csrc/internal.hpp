@@ -65,12 +65,15 @@ hipError_t launch_receive_rows(const int32_t* src_counts, const int32_t* src_off
 // ---- grouped SwiGLU FFN and dense linear (gemm.hip)
 size_t ffn_ws_bytes(int dtype, int64_t max_rows, int ffn, int d);
 // rows_in: gate/up reads input row rows_in[i] (NULL: row i); rows_out: down
-// writes output row rows_out[i] (NULL: row i).
+// writes output row rows_out[i] (NULL: row i).  likely_rows: rows the groups
+// hold when every expert is equally popular, where max_rows may be a loose
+// bound (0: max_rows); picks kernels only.
 hipError_t launch_grouped_ffn(int dtype, int n_groups, int ffn, int d, const void* in,
                               const int32_t* rows_in, const int32_t* rows_out,
                               const int32_t* goff, int64_t max_rows,
                               const void* w_gate_up, const void* w_down, void* out, void* ws,
-                              hipStream_t s, int prof_gate_up);  // profile id of gate/up, down = +1; -1: none
+                              hipStream_t s, int prof_gate_up,   // profile id of gate/up, down = +1; -1: none
+                              int64_t likely_rows = 0);
 // FP8 (E4M3) experts: row quantisation, and the grouped SwiGLU FFN on
 // quantised operands (x and the weights by row scales; H is quantised per
 // row between the passes, inside the workspace).

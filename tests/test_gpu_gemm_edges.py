@@ -159,3 +159,25 @@ def test_ffn_fp8_tall_tiles(counts, d, F, gather):
     rest = torch.ones(n_src, dtype=torch.bool, device=DEV)
     rest[at] = False
     assert out[rest].isnan().all()
+
+
+# a row bound of all token slots over the 8 experts of 64 that are here: both
+# sides of the tile rule on the rows they likely hold (892 and 900), groups
+# far shorter and longer than that
+@pytest.mark.parametrize("n_tokens", [1190, 1200])
+def test_gathered_loose_bound(n_tokens):
+    counts, d, F, bound = [1, 0, 193, 64, 300, 17, 129, 196], 2048, 1408, n_tokens * 6
+    X, rows, goff, wgu, wd, _ = ffn_case("bf16", counts, d, F, True)
+    desc = L.make_desc(CONFIGS["tiny"].scaled(n_tokens=n_tokens, hidden=d, n_experts=64, top_k=6,
+                                              ffn=F, dtype="bf16"))
+    y = torch.full((bound, d), float("nan"), dtype=torch.bfloat16, device=DEV)
+    ws = torch.empty(L.fs_workspace_size(desc, L.FS_OP_GROUPED_FFN, bound, F), dtype=torch.uint8,
+                     device=DEV)
+    gat = torch.zeros(bound, dtype=torch.int32, device=DEV)
+    gat[:len(rows)] = rows
+    L.fs_grouped_expert_ffn_gathered(desc, len(counts), F, X, gat, torch.tensor(goff, device=DEV),
+                                     bound, wgu, wd, y, ws)
+    torch.cuda.synchronize()
+    Xr, M = X[rows.long()], int(goff[-1])
+    assert bool(torch.isnan(y[M:]).all())
+    check_ffn("bf16", Xr, None, goff, wgu, wd, y[:M])
