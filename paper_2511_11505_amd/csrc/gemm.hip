@@ -24,6 +24,7 @@
 #include "common.hpp"
 #include "gemm_common.hpp"
 #include "internal.hpp"
+#include "pass_rules.hpp"
 
 namespace fs {
 namespace {
@@ -909,7 +910,6 @@ __global__ __launch_bounds__(256) void fragment_order_fp8_kernel(const uint8_t* 
 // epilogue runs here; with several, each slice stores fp32 partials
 // P[slice][row][col] and stream_reduce_kernel sums them in slice order.
 constexpr int kStreamWrows = 64;       // weight rows per workgroup
-constexpr int kStreamMaxRows = 4096;   // larger batches use the LDS-ring kernels
 // workgroups aimed for: about two waves per CU keep enough loads in flight,
 // while every extra K slice adds fp32 partials of all the pass's rows
 // (decode shared expert: 2048 -> 512 took gate/up 44 -> 29 us, down 33 ->
@@ -1174,32 +1174,6 @@ int num_cus() {
   return cus;
 }
 
-// Tile variant of the LDS-ring GEMMs, per pass: the interleaved 128 x 256
-// x 64 ring with eight waves (5) for every shape, except down passes whose
-// output width is a multiple of 128 but not of 256 (10: 128 x 128 tiles).
-// Measured against it and dropped (block steps, same box):
-// - a register-staged 256 x 256 kernel on dense gate/up (Llama-4-Scout-shaped
-//   shared expert 1317 -> 1232 us for the ring);
-// - 256-row tiles on routed passes, whose half-empty tail tiles waste MFMA
-//   work;
-// - 256 x 256 tiles (eight waves of 128 x 64, two 64 KB slots, 16 x 16 x 32
-//   MFMAs) on dense passes.  Alone they are faster on the DeepSeek-V3-shaped
-//   shared expert (gate/up 195 -> 184 us, down 119 -> 111 us), but their
-//   workgroups hold a whole CU's registers, and in the block, where the
-//   shared passes run beside the Dispatch stand-in copy, the copy's cost
-//   moves to whichever pass it overlaps: gate/up alone on them, 380 -> 230
-//   us, shared down 133 -> 399 us, step 3.78 -> 3.93 ms.  Llama-4-Scout-shaped
-//   shared gate/up (eight rounds of tiles) 1215 -> 1402 us;
-// - two K groups of four waves on the 128 x 256 tile (each wave 64 x 128
-//   over every other 32-wide K step, partial sums added in LDS): a quarter
-//   fewer LDS fragment reads, yet Llama-4-Scout-shaped routed gate/up 1390
-//   -> 1408 us, DeepSeek-V3-shaped down 977 -> 1050 us.
-// nout: output columns of the pass (F for gate/up, d for down).
-int tile_choice(bool down, int nout) {
-  if (down && nout % 256 != 0) return 10;   // the only down variant for such widths
-  return 5;
-}
-
 // occ workgroups per compute unit (capped by the tile count, a multiple of 8).
 int64_t persistent_grid(int64_t max_rows, int G, int BM, int nn, int occ) {
   const int cus = num_cus();
@@ -1298,90 +1272,6 @@ int stream_splits(int64_t max_rows, int G, int nw, int K, size_t partial_bytes) 
   return s < 1 ? 1 : (int)s;
 }
 
-// The streaming kernel takes a pass when its groups average at most 64 rows
-// and the LDS-ring kernel's 128 x 256 tiles would not give every CU one.
-bool use_stream(int dtype, int64_t max_rows, int G, int ffn, int d) {
-  if (dtype != 1 || max_rows > kStreamMaxRows || max_rows > (int64_t)64 * G || ffn % 64 != 0 ||
-      d % 64 != 0)
-    return false;
-  const int64_t ring_tiles =
-      (int64_t)G * std::max<int64_t>(1, cdiv64(max_rows, (int64_t)128 * G)) * std::max(1, ffn / 128);
-  return ring_tiles < 256;
-}
-
-// Largest tile height of a pass on the 192-row tiles.  Of one dense group,
-// whose rows the host knows: the height whose rounds of tiles over the CUs
-// (each costing its rows, and a fixed part worth about 32) are shortest.
-// Routed groups take 192: their sizes, and so the rounds, are known on the
-// device only.
-int r192_height(int64_t max_rows, int G, int n_tiles, int unit = 32) {
-  if (G > 1) return 192;
-  int best = 192;
-  int64_t best_cost = -1;
-  for (int h = 192; h >= 128; h -= unit) {
-    const int64_t t = cdiv64(max_rows, h), height = cdiv64(cdiv64(max_rows, t), unit) * unit;
-    const int64_t cost = cdiv64(t * n_tiles, num_cus()) * (height + 32);
-    if (best_cost < 0 || cost < best_cost) {
-      best_cost = cost;
-      best = h;
-    }
-  }
-  return best;
-}
-
-// The 192-row tiles take the passes whose groups average at least 112 rows and
-// whose 128-row ring tiles would give every CU one (below that the ring splits
-// K).  64 groups, d 2048, F 1408, gate/up + down: 96 rows a group 169 + 79 us
-// on the ring, 168 + 81 us on these tiles; 128 rows 216 + 114 and 180 + 87;
-// 384 rows 367 + 209 and 330 + 197.  32 groups of 1024 rows, d 7168, F 2048:
-// 1755 + 978 and 1690 + 829 (FP8 916 + 565 and 860 + 470).  One group of 8192 rows, gate/up of d 5120,
-// F 8192: 1228 -> 998 us (1.38 PFLOP/s).
-// rows are the likely ones where the bound is loose: 1300 replicated tokens, 160
-// experts top-6, 20 of them here, d 5120 (a bound of 390 rows a group, 49 of
-// them real): layer 452 us when the bound decides, 449 us so (441 to 446 us
-// before there were 192-row tiles); 2000 tokens 508 and 504 us.
-bool r192_ok(int64_t rows, int G, int k_blocks, int64_t ring_tiles) {
-  return rows >= (int64_t)112 * G && ring_tiles >= num_cus() && k_blocks >= 4;
-}
-
-// Kernel of one pass (gate/up: NOUT = F, K = d; down: NOUT = d, K = F).
-enum PassKind { PASS_R64, PASS_STREAM, PASS_RING, PASS_R192 };
-
-// The 64-row tiles (gemm_r64.hip) take fp32, widths the ring's tiles do not
-// divide, and, of the bf16 passes that others could take as well:
-// - grouped FFNs of at most 48 rows a group, hidden size below 4096: a
-//   128-row tile is then mostly padding.  64 groups, d 2048, F 1408, gate/up
-//   + down: 6 rows a group 146 + 68 us on the ring, 137 + 65 us on 64-row
-//   tiles; 31 rows 160 + 71 and 148 + 70; but 66 rows 169 + 76 and 177 + 95,
-//   and 32 groups of 16 rows, d 7168, F 2048: 295 + 163 and 301 + 179;
-// - one dense group whose 128 x 256 ring tiles would leave CUs idle and K be
-//   split, for K below 4096 (us with the split and its reduction -> on 64-row
-//   tiles): d 2048, F 2816, gate/up + down, 333 rows 42 + 24 -> 22 + 16, 1365
-//   rows 64 + 60 -> 58 + 38; down of d 7168, F 2048: 64 rows 18 -> 16, 333
-//   rows 52 -> 34, 1000 rows 69 -> 62.  A long K needs the split: gate/up of
-//   that shape, 64 rows 30 -> 41, 1000 rows 135 -> 141;
-// - unless the rows fit one tile and the weight tiles alone occupy enough CUs
-//   (more than a quarter): d 5120, F 8192, 64 rows: gate/up 60 -> 39 (256
-//   tiles), down 59 -> 43 (80 tiles).
-PassKind pass_kind(int dtype, bool gateup, int64_t max_rows, int64_t likely_rows, int G, int ffn,
-                   int d) {
-  if (dtype != 1) return PASS_R64;
-  const int NOUT = gateup ? ffn : d, K = gateup ? d : ffn;
-  const bool stream = use_stream(dtype, max_rows, G, ffn, d);
-  if (G == 1) {
-    const int64_t ring_tiles = cdiv64(max_rows, 128) * (NOUT / (gateup ? 128 : 256));
-    if (ring_tiles < num_cus() &&
-        (K < 4096 || (max_rows <= 64 && NOUT / (gateup ? 32 : 64) > num_cus() / 4)))
-      return PASS_R64;
-  } else if (!stream && max_rows <= (int64_t)48 * G && d < 4096) {
-    return PASS_R64;
-  }
-  if (stream) return PASS_STREAM;
-  if (ffn % 128 != 0 || d % 256 != 0) return PASS_R64;
-  const int64_t ring_tiles = G * cdiv64(max_rows, (int64_t)128 * G) * (NOUT / (gateup ? 128 : 256));
-  return r192_ok(likely_rows, G, K / 64, ring_tiles) ? PASS_R192 : PASS_RING;
-}
-
 // One FP8 GEMM pass on 128 x 256 tiles, eight waves of 64 x 64 (as bf16:
 // routed gate/up of the DeepSeek-V3-shaped prefill 1000 -> 955 us, down
 // 660 -> 616 us against four waves of 64 x 128).  Measured on the routed
@@ -1467,11 +1357,9 @@ hipError_t launch_grouped_ffn_fp8(int G, int ffn, int d, const uint8_t* x, const
                   const float* sw, int K, int NOUT, bf16_t* c) {
     constexpr int MODE = decltype(M)::value;
     constexpr bool gateup = MODE == MODE_GATEUP;
-    const int64_t ring_tiles =
-        G * cdiv64(max_rows, (int64_t)128 * G) * (NOUT / (gateup ? 128 : 256));
-    if (r192_ok(max_rows, G, K / 128, ring_tiles)) {
+    if (pass_kind_fp8(gateup, max_rows, G, ffn, d, num_cus()) == PASS_R192) {
       launch_r192_fp8(gateup, a, rows, goff, G, max_rows, w, K, NOUT, c, NOUT, num_cus(),
-                      r192_height(max_rows, G, NOUT / (gateup ? 128 : 256), 64), sa, sw, s);
+                      r192_height(max_rows, G, NOUT / (gateup ? 128 : 256), num_cus(), 64), sa, sw, s);
       return;
     }
     const KSplit sp =
@@ -1510,11 +1398,11 @@ hipError_t launch_grouped_ffn(int dtype, int G, int ffn, int d, const void* in,
   auto pass = [&](auto M, const void* a, const int32_t* rows, const void* w, int K, int NOUT, void* c) {
     constexpr int MODE = decltype(M)::value;
     constexpr bool gateup = MODE == MODE_GATEUP;
-    const PassKind kind = pass_kind(dtype, gateup, max_rows, likely_rows, G, ffn, d);
+    const PassKind kind = pass_kind(dtype, gateup, max_rows, likely_rows, G, ffn, d, num_cus());
     if (kind == PASS_R64) {
       launch_gemm_r64(dtype, gateup, a, rows, goff, G, max_rows, w, K, NOUT, c, NOUT, num_cus(), s);
     } else if (kind == PASS_R192) {
-      const int hmax = r192_height(max_rows, G, NOUT / (gateup ? 128 : 256));
+      const int hmax = r192_height(max_rows, G, NOUT / (gateup ? 128 : 256), num_cus());
       (gateup ? launch_r192_gateup : launch_r192_down)(a, rows, goff, G, max_rows, w, K, NOUT, c, NOUT,
                                                        num_cus(), hmax, s);
     } else if (kind == PASS_RING) {
@@ -1637,15 +1525,12 @@ hipError_t launch_grouped_ffn_fo_fp8(int G, int ffn, int d, const uint8_t* x, co
 hipError_t launch_dense_linear(int dtype, int m, int n, int kdim, const void* a, const void* w,
                                void* out, hipStream_t s) {
   if (m <= 0) return hipSuccess;
-  // one group of m rows: 64-row tiles where the ring's would leave CUs idle
-  // (see pass_kind), else the 192-row tiles, else the LDS ring (128 x 128
-  // tiles when n is not a multiple of 256)
-  const int64_t ring_tiles = cdiv64(m, 128) * (n / (n % 256 == 0 ? 256 : 128));
-  if (dtype != 1 || (ring_tiles < num_cus() && kdim < 4096))
+  const PassKind kind = dense_kind(dtype, m, n, kdim, num_cus());
+  if (kind == PASS_R64)
     launch_gemm_r64(dtype, false, a, nullptr, nullptr, 1, m, w, kdim, n, out, n, num_cus(), s);
-  else if (n % 256 == 0 && r192_ok(m, 1, kdim / 64, ring_tiles))
+  else if (kind == PASS_R192)
     launch_r192_down(a, nullptr, nullptr, 1, m, w, kdim, n, out, n, num_cus(),
-                     r192_height(m, 1, n / 256), s);
+                     r192_height(m, 1, n / 256, num_cus()), s);
   else
     gemm_pass<MODE_DOWN>(tile_choice(true, n), (const bf16_t*)a, nullptr, nullptr, 1,
                          m, (const bf16_t*)w, kdim, n, (bf16_t*)out, n, s);

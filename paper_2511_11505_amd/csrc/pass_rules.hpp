@@ -1,0 +1,143 @@
+// Which kernel runs a pass of the grouped GEMM.  Plain C++, so that the rules
+// can be built and checked without a GPU; cus is the number of compute units.
+#pragma once
+
+#include <stdint.h>
+
+#include <algorithm>
+
+namespace fs {
+namespace {
+
+inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
+constexpr int kStreamMaxRows = 4096;   // larger batches use the LDS-ring kernels
+
+// The streaming kernel takes a pass when its groups average at most 64 rows
+// and the LDS-ring kernel's 128 x 256 tiles would not give every CU one.
+inline bool use_stream(int dtype, int64_t max_rows, int G, int ffn, int d) {
+  if (dtype != 1 || max_rows > kStreamMaxRows || max_rows > (int64_t)64 * G || ffn % 64 != 0 ||
+      d % 64 != 0)
+    return false;
+  const int64_t ring_tiles =
+      (int64_t)G * std::max<int64_t>(1, cdiv(max_rows, (int64_t)128 * G)) * std::max(1, ffn / 128);
+  return ring_tiles < 256;
+}
+
+// Largest tile height of a pass on the 192-row tiles.  Of one dense group,
+// whose rows the host knows: the height whose rounds of tiles over the CUs
+// (each costing its rows, and a fixed part worth about 32) are shortest.
+// Routed groups take 192: their sizes, and so the rounds, are known on the
+// device only.
+inline int r192_height(int64_t max_rows, int G, int n_tiles, int cus, int unit = 32) {
+  if (G > 1) return 192;
+  int best = 192;
+  int64_t best_cost = -1;
+  for (int h = 192; h >= 128; h -= unit) {
+    const int64_t t = cdiv(max_rows, h), height = cdiv(cdiv(max_rows, t), unit) * unit;
+    const int64_t cost = cdiv(t * n_tiles, cus) * (height + 32);
+    if (best_cost < 0 || cost < best_cost) {
+      best_cost = cost;
+      best = h;
+    }
+  }
+  return best;
+}
+
+// The 192-row tiles take the passes whose groups average at least 112 rows and
+// whose 128-row ring tiles would give every CU one (below that the ring splits
+// K).  64 groups, d 2048, F 1408, gate/up + down: 96 rows a group 169 + 79 us
+// on the ring, 168 + 81 us on these tiles; 128 rows 216 + 114 and 180 + 87;
+// 384 rows 367 + 209 and 330 + 197.  32 groups of 1024 rows, d 7168, F 2048:
+// 1755 + 978 and 1690 + 829 (FP8 916 + 565 and 860 + 470).  One group of 8192 rows, gate/up of d 5120,
+// F 8192: 1228 -> 998 us (1.38 PFLOP/s).
+// rows are the likely ones where the bound is loose: 1300 replicated tokens, 160
+// experts top-6, 20 of them here, d 5120 (a bound of 390 rows a group, 49 of
+// them real): layer 452 us when the bound decides, 449 us so (441 to 446 us
+// before there were 192-row tiles); 2000 tokens 508 and 504 us.
+inline bool r192_ok(int64_t rows, int G, int k_blocks, int64_t ring_tiles, int cus) {
+  return rows >= (int64_t)112 * G && ring_tiles >= cus && k_blocks >= 4;
+}
+
+// Kernel of one pass (gate/up: NOUT = F, K = d; down: NOUT = d, K = F).
+enum PassKind { PASS_R64, PASS_STREAM, PASS_RING, PASS_R192 };
+
+// The 64-row tiles (gemm_r64.hip) take fp32, widths the ring's tiles do not
+// divide, and, of the bf16 passes that others could take as well:
+// - grouped FFNs of at most 48 rows a group, hidden size below 4096: a
+//   128-row tile is then mostly padding.  64 groups, d 2048, F 1408, gate/up
+//   + down: 6 rows a group 146 + 68 us on the ring, 137 + 65 us on 64-row
+//   tiles; 31 rows 160 + 71 and 148 + 70; but 66 rows 169 + 76 and 177 + 95,
+//   and 32 groups of 16 rows, d 7168, F 2048: 295 + 163 and 301 + 179;
+// - one dense group whose 128 x 256 ring tiles would leave CUs idle and K be
+//   split, for K below 4096 (us with the split and its reduction -> on 64-row
+//   tiles): d 2048, F 2816, gate/up + down, 333 rows 42 + 24 -> 22 + 16, 1365
+//   rows 64 + 60 -> 58 + 38; down of d 7168, F 2048: 64 rows 18 -> 16, 333
+//   rows 52 -> 34, 1000 rows 69 -> 62.  A long K needs the split: gate/up of
+//   that shape, 64 rows 30 -> 41, 1000 rows 135 -> 141;
+// - unless the rows fit one tile and the weight tiles alone occupy enough CUs
+//   (more than a quarter): d 5120, F 8192, 64 rows: gate/up 60 -> 39 (256
+//   tiles), down 59 -> 43 (80 tiles).
+inline PassKind pass_kind(int dtype, bool gateup, int64_t max_rows, int64_t likely_rows, int G,
+                          int ffn, int d, int cus) {
+  if (dtype != 1) return PASS_R64;
+  const int NOUT = gateup ? ffn : d, K = gateup ? d : ffn;
+  const bool stream = use_stream(dtype, max_rows, G, ffn, d);
+  if (G == 1) {
+    const int64_t ring_tiles = cdiv(max_rows, 128) * (NOUT / (gateup ? 128 : 256));
+    if (ring_tiles < cus &&
+        (K < 4096 || (max_rows <= 64 && NOUT / (gateup ? 32 : 64) > cus / 4)))
+      return PASS_R64;
+  } else if (!stream && max_rows <= (int64_t)48 * G && d < 4096) {
+    return PASS_R64;
+  }
+  if (stream) return PASS_STREAM;
+  if (ffn % 128 != 0 || d % 256 != 0) return PASS_R64;
+  const int64_t ring_tiles = G * cdiv(max_rows, (int64_t)128 * G) * (NOUT / (gateup ? 128 : 256));
+  return r192_ok(likely_rows, G, K / 64, ring_tiles, cus) ? PASS_R192 : PASS_RING;
+}
+
+// An FP8 pass: the ring or the 192-row tiles.
+inline PassKind pass_kind_fp8(bool gateup, int64_t max_rows, int G, int ffn, int d, int cus) {
+  const int NOUT = gateup ? ffn : d, K = gateup ? d : ffn;
+  const int64_t ring_tiles = G * cdiv(max_rows, (int64_t)128 * G) * (NOUT / (gateup ? 128 : 256));
+  return r192_ok(max_rows, G, K / 128, ring_tiles, cus) ? PASS_R192 : PASS_RING;
+}
+
+// A dense linear, one group of m rows: 64-row tiles where the ring's would
+// leave CUs idle (as pass_kind), else the 192-row tiles, else the ring (128 x
+// 128 tiles when n is not a multiple of 256).
+inline PassKind dense_kind(int dtype, int m, int n, int kdim, int cus) {
+  const int64_t ring_tiles = cdiv(m, 128) * (n / (n % 256 == 0 ? 256 : 128));
+  if (dtype != 1 || (ring_tiles < cus && kdim < 4096)) return PASS_R64;
+  return n % 256 == 0 && r192_ok(m, 1, kdim / 64, ring_tiles, cus) ? PASS_R192 : PASS_RING;
+}
+
+// Tile variant of the LDS-ring GEMMs, per pass: the interleaved 128 x 256
+// x 64 ring with eight waves (5) for every shape, except down passes whose
+// output width is a multiple of 128 but not of 256 (10: 128 x 128 tiles).
+// Measured against it and dropped (block steps, same box):
+// - a register-staged 256 x 256 kernel on dense gate/up (Llama-4-Scout-shaped
+//   shared expert 1317 -> 1232 us for the ring);
+// - 256-row tiles on routed passes, whose half-empty tail tiles waste MFMA
+//   work;
+// - 256 x 256 tiles (eight waves of 128 x 64, two 64 KB slots, 16 x 16 x 32
+//   MFMAs) on dense passes.  Alone they are faster on the DeepSeek-V3-shaped
+//   shared expert (gate/up 195 -> 184 us, down 119 -> 111 us), but their
+//   workgroups hold a whole CU's registers, and in the block, where the
+//   shared passes run beside the Dispatch stand-in copy, the copy's cost
+//   moves to whichever pass it overlaps: gate/up alone on them, 380 -> 230
+//   us, shared down 133 -> 399 us, step 3.78 -> 3.93 ms.  Llama-4-Scout-shaped
+//   shared gate/up (eight rounds of tiles) 1215 -> 1402 us;
+// - two K groups of four waves on the 128 x 256 tile (each wave 64 x 128
+//   over every other 32-wide K step, partial sums added in LDS): a quarter
+//   fewer LDS fragment reads, yet Llama-4-Scout-shaped routed gate/up 1390
+//   -> 1408 us, DeepSeek-V3-shaped down 977 -> 1050 us.
+// nout: output columns of the pass (F for gate/up, d for down).
+inline int tile_choice(bool down, int nout) {
+  if (down && nout % 256 != 0) return 10;   // the only down variant for such widths
+  return 5;
+}
+
+}  // namespace
+}  // namespace fs

@@ -1,0 +1,39 @@
+"""The dispatch rules of csrc/pass_rules.hpp, built with the host compiler."""
+
+import ctypes
+import functools
+import os
+import subprocess
+import tempfile
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(HERE, "..", "paper_2511_11505_amd", "csrc")
+R64, STREAM, RING, R192 = range(4)
+CUS = 256   # of gfx950
+
+
+@functools.lru_cache(maxsize=None)
+def _lib():
+    with tempfile.TemporaryDirectory() as d:
+        so = os.path.join(d, "rules.so")
+        subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", CSRC, "-o", so,
+                        os.path.join(HERE, "pass_rules_shim.cpp")], check=True)
+        lib = ctypes.CDLL(so)
+    i, q = ctypes.c_int, ctypes.c_longlong
+    lib.rule_pass.argtypes = [i, i, q, q, i, i, i, i]
+    lib.rule_pass_fp8.argtypes = [i, q, i, i, i, i]
+    lib.rule_dense.argtypes = [i] * 5
+    return lib
+
+
+def pass_kind(gateup, rows, G, ffn, d, dtype="bf16", likely=None, cus=CUS):
+    return _lib().rule_pass(int(dtype == "bf16"), int(gateup), rows, rows if likely is None else likely,
+                            G, ffn, d, cus)
+
+
+def pass_kind_fp8(gateup, rows, G, ffn, d, cus=CUS):
+    return _lib().rule_pass_fp8(int(gateup), rows, G, ffn, d, cus)
+
+
+def dense_kind(m, n, kdim, dtype="bf16", cus=CUS):
+    return _lib().rule_dense(int(dtype == "bf16"), m, n, kdim, cus)
