@@ -97,6 +97,14 @@ __device__ __forceinline__ float wave_sum(float v) {
   v += dpp_f<kDppMirror>(v);
   return (lane_f(v, 0) + lane_f(v, 16)) + (lane_f(v, 32) + lane_f(v, 48));
 }
+__device__ __forceinline__ int wave_sum_i(int v) {
+  v += dpp_i<kDppXor1>(v);
+  v += dpp_i<kDppXor2>(v);
+  v += dpp_i<kDppHalfMirror>(v);
+  v += dpp_i<kDppMirror>(v);
+  return (__builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16)) +
+         (__builtin_amdgcn_readlane(v, 32) + __builtin_amdgcn_readlane(v, 48));
+}
 // Arg-max of (key, idx): larger key wins, equal keys go to the lower idx.
 // Bitwise | and & evaluate both comparisons, so this is a compare and two
 // selects; a short-circuit || / && compiles to exec-mask branches, a serial

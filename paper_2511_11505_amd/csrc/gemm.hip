@@ -1402,7 +1402,7 @@ hipError_t launch_grouped_ffn(int dtype, int G, int ffn, int d, const void* in,
     if (kind == PASS_R64) {
       launch_gemm_r64(dtype, gateup, a, rows, goff, G, max_rows, w, K, NOUT, c, NOUT, num_cus(), s);
     } else if (kind == PASS_R192) {
-      const int hmax = r192_height(max_rows, G, NOUT / (gateup ? 128 : 256), num_cus());
+      const int hmax = r192_height(likely_rows, G, NOUT / (gateup ? 128 : 256), num_cus());
       (gateup ? launch_r192_gateup : launch_r192_down)(a, rows, goff, G, max_rows, w, K, NOUT, c, NOUT,
                                                        num_cus(), hmax, s);
     } else if (kind == PASS_RING) {

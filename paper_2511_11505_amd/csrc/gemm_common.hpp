@@ -18,19 +18,23 @@ __device__ __forceinline__ float swiglu_bf16_epi(float g, float u) {
   return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u;
 }
 
-// Group offsets and the exclusive prefix of m-tiles (of BM rows) per group, in
-// LDS.
+// Group offsets in LDS, clamped to [0, m_total]: rows past the host bound are
+// never read or written, so a short bound cannot overrun the H workspace.
 template <int NT>
-__device__ void sched_setup(const int32_t* __restrict__ goff, int G, int64_t m_total,
-                            int* s_goff, int* s_tpre, int* s_wtot, int BM) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // Offsets are clamped to [0, m_total]: rows past the host bound are never
-  // read or written, so a short bound cannot overrun the H workspace.
-  for (int g = tid; g <= G; g += NT) {
+__device__ void sched_offsets(const int32_t* __restrict__ goff, int G, int64_t m_total,
+                              int* s_goff) {
+  for (int g = threadIdx.x; g <= G; g += NT) {
     int v = goff ? goff[g] : (g == 0 ? 0 : (int)m_total);
     s_goff[g] = v < 0 ? 0 : (v > (int)m_total ? (int)m_total : v);
   }
   __syncthreads();
+}
+
+// The exclusive prefix of m-tiles (of BM rows) per group, in LDS, from the
+// offsets.
+template <int NT>
+__device__ void sched_tiles(int G, const int* s_goff, int* s_tpre, int* s_wtot, int BM) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   constexpr int IPT = (kMaxGroups + 1 + NT - 1) / NT;
   int cnt[IPT];
   int local = 0;
@@ -64,7 +68,8 @@ __device__ void sched_setup(const int32_t* __restrict__ goff, int G, int64_t m_t
 template <int NT, int BM>
 __device__ __forceinline__ void sched_setup(const int32_t* __restrict__ goff, int G, int64_t m_total,
                                             int* s_goff, int* s_tpre, int* s_wtot) {
-  sched_setup<NT>(goff, G, m_total, s_goff, s_tpre, s_wtot, BM);
+  sched_offsets<NT>(goff, G, m_total, s_goff);
+  sched_tiles<NT>(G, s_goff, s_tpre, s_wtot, BM);
 }
 
 // Largest g in [0, G) with nn * tpre[g] <= L.

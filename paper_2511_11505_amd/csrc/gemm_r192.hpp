@@ -12,8 +12,11 @@
 // v_mfma_f32_16x16x32_bf16, 192 accumulators; an LDS fragment read feeds six
 // or eight MFMAs.
 //
-//   Heights  A group's tiles have equal heights, a multiple of 32 up to 192,
-//            so the last tile is not a stub; the tile's code is one loop per
+//   Heights  The pass's largest height is 192, 160 or 128 rows: of one dense
+//            group the host chooses it, of routed groups, whose sizes the host
+//            does not know, every workgroup (tall_height; about 0.5 us).  A
+//            group's tiles have equal heights, a multiple of 32 up to that, so
+//            the last tile is not a stub; the tile's code is one loop per
 //            height (no branch inside).  A wave's 16-row fragments alternate
 //            between the two wave rows.  (224 and 256 rows make the compiler
 //            move accumulators in and out of the AGPRs inside the loop: 32
@@ -47,6 +50,7 @@
 
 #include "gemm_common.hpp"
 #include "internal.hpp"
+#include "tall_tiles.hpp"
 
 namespace fs {
 namespace {
@@ -113,6 +117,7 @@ __global__ __launch_bounds__(256, 1) void gemm_r192_kernel(
   __shared__ int s_goff[kMaxGroups + 1];
   __shared__ int s_tpre[kMaxGroups + 1];
   __shared__ int s_wtot[NT / 64];
+  __shared__ int s_cnt[NT / 64][3];
   __shared__ __align__(16) int s_rows[NT];         // row indices of a tile
   __shared__ __align__(16) float s_sa[F8 ? NT : 4], s_sb[F8 ? NT : 4];   // its scales
   __shared__ __align__(1024) unsigned char ring[2 * ASTAGE + 3 * BSTAGE];
@@ -122,8 +127,29 @@ __global__ __launch_bounds__(256, 1) void gemm_r192_kernel(
   const int wm = wave >> 1, wn = wave & 1;
   const int lr = lane & (FR - 1), lh = lane / FR;  // fragment row, K part (and column part)
   auto uni = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
-  sched_setup<NT>(goff, G, m_total, s_goff, s_tpre, s_wtot, hmax);
   const int nn = NOUT / NCOL;
+  sched_offsets<NT>(goff, G, m_total, s_goff);
+  if (hmax == 0) {
+    // the pass's largest tile height, from the m-tiles of all groups at each
+    int cnt[3] = {0, 0, 0};
+    for (int g = tid; g < G; g += NT) {
+      const int n = max(s_goff[g + 1] - s_goff[g], 0);
+      cnt[0] += (n + 191) / 192;
+      if constexpr (!F8) cnt[1] += (n + 159) / 160;
+      cnt[2] += (n + 127) / 128;
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      const int n = wave_sum_i(cnt[i]);
+      if (lane == 0) s_cnt[wave][i] = n;
+    }
+    __syncthreads();
+    int t[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) t[i] = uni(s_cnt[0][i] + s_cnt[1][i] + s_cnt[2][i] + s_cnt[3][i]);
+    hmax = uni(tall_height(uni(s_goff[G] - s_goff[0]), t[0], t[1], t[2], nn, (int)gridDim.x));
+  }
+  sched_tiles<NT>(G, s_goff, s_tpre, s_wtot, hmax);
   const int64_t total = (int64_t)nn * uni(s_tpre[G]);
   const int64_t per_xcd = (total + kXcd - 1) / kXcd;
   const int64_t xcd_base = (int64_t)(blockIdx.x % kXcd) * per_xcd;
@@ -171,19 +197,13 @@ __global__ __launch_bounds__(256, 1) void gemm_r192_kernel(
     it.g = uni(find_group_from(s_tpre, G, nn, L, ghint));
     ghint = it.g;
     const int Tg = uni(s_tpre[it.g + 1]) - uni(s_tpre[it.g]);
-    int local = uni((int)(L - (int64_t)nn * s_tpre[it.g]));
-    // m-tiles in bands of at most 8, a band's m-tiles fastest, then the
-    // n-tiles: the tiles an XCD runs together share both operands
-    const int bands = uni((Tg + 7) / 8), bh = uni((Tg + bands - 1) / bands);
-    const int band = uni(local / (nn * bh));
-    local -= band * nn * bh;
-    const int bw = min(bh, Tg - band * bh);
-    const int nt = uni(local / bw), mt = band * bh + local - nt * bw;
+    const int local = uni((int)(L - (int64_t)nn * s_tpre[it.g]));
+    int mt, nt;
+    tall_order(local, Tg, nn, mt, nt);
     it.n0 = nt * NCOL;
     it.row_base = uni(s_goff[it.g]);
     const int rows_g = uni(s_goff[it.g + 1]) - it.row_base;
-    // the group's tiles have equal heights, a multiple of HU rows
-    const int h = uni((rows_g + Tg - 1) / Tg + HU - 1) & ~(HU - 1);
+    const int h = tall_rows(rows_g, Tg, HU);
     it.m0 = mt * h;
     it.rows_t = min(rows_g - it.m0, h);
     it.tma = max(TMIN, (it.rows_t + HU - 1) / HU);
@@ -476,7 +496,7 @@ void run_r192(const void* A, const int32_t* rows, const int32_t* goff, int G, in
               const void* B, int K, int NOUT, void* C, int ldc, int cus, int hmax, const float* sA,
               const float* sB, hipStream_t s) {
   using TE = typename std::conditional<F8, uint8_t, bf16_t>::type;
-  const int64_t tiles = (cdiv64(m_total, hmax) + G) * (NOUT / (MODE == MODE_GATEUP ? 128 : 256));
+  const int64_t tiles = (cdiv64(m_total, hmax ? hmax : 128) + G) * (NOUT / (MODE == MODE_GATEUP ? 128 : 256));
   const int64_t grid = std::min<int64_t>(cdiv64(tiles, kXcd), cdiv64(cus, kXcd)) * kXcd;
   launch_k(gemm_r192_kernel<MODE, F8>, (unsigned)grid, 256, 0, s, (const TE*)A, rows, goff, G,
            m_total, (const TE*)B, K, NOUT, (bf16_t*)C, ldc, hmax, sA, sB);

@@ -95,13 +95,14 @@ void launch_gemm_r64(int dtype, bool gateup, const void* A, const int32_t* rows,
                      const int32_t* goff, int G, int64_t m_total, const void* B, int K, int NOUT,
                      void* C, int ldc, int cus, hipStream_t s);
 // One FP8 pass on tiles of up to 192 x 256 (gemm_r192.hpp): operands, scales and
-// widths as launch_grouped_ffn_fp8's, K >= 512; hmax 128 or 192.
+// widths as launch_grouped_ffn_fp8's, K >= 512; hmax 128 or 192, or 0 as below.
 void launch_r192_fp8(bool gateup, const uint8_t* A, const int32_t* rows, const int32_t* goff, int G,
                      int64_t m_total, const uint8_t* B, int K, int NOUT, void* C, int ldc, int cus,
                      int hmax, const float* sA, const float* sB, hipStream_t s);
 // One bf16 pass on tiles of up to 192 x 256 (gemm_r192.hpp): K % 64 == 0, K >= 256,
 // NOUT % 128 == 0 (gate/up) or % 256 == 0 (down).
-// hmax: largest tile height, 128, 160 or 192 rows.
+// hmax: largest tile height, 128, 160 or 192 rows, or 0: chosen on the device
+// from the groups' sizes.
 void launch_r192_gateup(const void* A, const int32_t* rows, const int32_t* goff, int G,
                         int64_t m_total, const void* B, int K, int NOUT, void* C, int ldc, int cus,
                         int hmax, hipStream_t s);

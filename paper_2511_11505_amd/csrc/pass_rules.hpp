@@ -27,10 +27,12 @@ inline bool use_stream(int dtype, int64_t max_rows, int G, int ffn, int d) {
 // Largest tile height of a pass on the 192-row tiles.  Of one dense group,
 // whose rows the host knows: the height whose rounds of tiles over the CUs
 // (each costing its rows, and a fixed part worth about 32) are shortest.
-// Routed groups take 192: their sizes, and so the rounds, are known on the
-// device only.
+// Of routed groups, whose sizes are known on the device only, 0: the kernel
+// chooses (tall_tiles.hpp), in about 0.5 us; but 192 where the rows make four
+// rounds of 128-row tiles and more, since the height then matters little: of 57
+// such passes in bf16, 192 rows never took more than 1.012 times the ring's time.
 inline int r192_height(int64_t max_rows, int G, int n_tiles, int cus, int unit = 32) {
-  if (G > 1) return 192;
+  if (G > 1) return max_rows * n_tiles >= (int64_t)4 * 128 * cus ? 192 : 0;
   int best = 192;
   int64_t best_cost = -1;
   for (int h = 192; h >= 128; h -= unit) {

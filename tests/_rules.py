@@ -1,4 +1,5 @@
-"""The dispatch rules of csrc/pass_rules.hpp, built with the host compiler."""
+"""The rules of csrc/pass_rules.hpp and csrc/tall_tiles.hpp, built with the
+host compiler."""
 
 import ctypes
 import functools
@@ -23,6 +24,9 @@ def _lib():
     lib.rule_pass.argtypes = [i, i, q, q, i, i, i, i]
     lib.rule_pass_fp8.argtypes = [i, q, i, i, i, i]
     lib.rule_dense.argtypes = [i] * 5
+    lib.rule_height.argtypes = [q, i, i, i, i]
+    lib.tall_height.argtypes = [i] * 6
+    lib.tall_rows.argtypes = [i] * 3
     return lib
 
 
@@ -37,3 +41,26 @@ def pass_kind_fp8(gateup, rows, G, ffn, d, cus=CUS):
 
 def dense_kind(m, n, kdim, dtype="bf16", cus=CUS):
     return _lib().rule_dense(int(dtype == "bf16"), m, n, kdim, cus)
+
+
+def tall_height(counts, n_cols, gateup, fp8=False, cus=CUS):
+    """Largest tile height of a pass of n_cols output columns over groups of
+    `counts` rows: the host's choice, or the 192-row kernel's."""
+    nn = n_cols // (128 if gateup else 256)
+    h = _lib().rule_height(sum(counts), len(counts), nn, cus, 64 if fp8 else 32)
+    if h:
+        return h
+    t = [0 if fp8 and h == 160 else sum(-(-n // h) for n in counts) for h in (192, 160, 128)]
+    wgs = min(-(-(-(-sum(counts) // 128) + len(counts)) * nn // 8), -(-cus // 8)) * 8
+    return _lib().tall_height(sum(counts), *t, nn, wgs)
+
+
+def tall_rows(rows, tiles, unit):
+    return _lib().tall_rows(rows, tiles, unit)
+
+
+def tall_order(tiles, nn):
+    a = (ctypes.c_int * (tiles * nn))()
+    b = (ctypes.c_int * (tiles * nn))()
+    _lib().tall_order(tiles, nn, a, b)
+    return list(zip(a, b))

@@ -1,5 +1,7 @@
-"""The dispatch rules of the GEMM passes, on the host: every kernel gets only
-widths that its tiles divide, over all sizes that the entry points accept."""
+"""The dispatch and tile rules of the GEMM passes, on the host: every kernel gets
+only widths that its tiles divide, over all sizes that the entry points accept;
+the 192-row kernel's tiles cover every group; and the routes of the shapes that
+lines of the rules were drawn by."""
 
 import random
 
@@ -39,3 +41,38 @@ def test_dense_kernels_take_their_widths():
         kind = R.dense_kind(m, n, kdim, cus=cus)
         assert kind in (R.R64, R.RING) or (kind == R.R192 and n % 256 == 0 and kdim >= 256)
         assert R.dense_kind(m, n - 64 or 64, kdim, dtype="f32", cus=cus) == R.R64
+
+
+@pytest.mark.parametrize("unit", [32, 64])
+@pytest.mark.parametrize("hmax", [128, 160, 192])
+def test_tall_tiles_cover_a_group(hmax, unit):
+    """Equal heights cover a group: no tile is empty or taller than allowed."""
+    if hmax % unit:
+        return
+    for rows in list(range(1, 3000)) + [59999, 60000]:
+        t = -(-rows // hmax)
+        h = R.tall_rows(rows, t, unit)
+        assert h % unit == 0 and h <= hmax and (t - 1) * h < rows <= t * h
+
+
+def test_tall_order_visits_every_tile_in_bands():
+    for tiles in list(range(1, 40)) + [63, 64, 65]:
+        for nn in (1, 3, 11):
+            at = R.tall_order(tiles, nn)
+            assert sorted(at) == [(m, n) for m in range(tiles) for n in range(nn)]
+            # a band of at most 8 m-tiles is finished before the next begins
+            for i in range(0, tiles * nn, 8 * nn):
+                assert len({m for m, _ in at[i:i + nn]}) <= 8
+
+
+# the height whose rounds of tiles over the CUs are shortest
+@pytest.mark.parametrize("counts,n_cols,gateup,fp8,want", [
+    ([180] * 12 + [200] * 4, 3840, False, False, 160),
+    ([370] * 8 + [100], 2048, True, False, 160),
+    ([300] * 8 + [50], 2048, True, False, 128),   # 17 m-tiles of 192 make 272 tiles, two rounds
+    ([300] * 8 + [50], 2048, True, True, 128),
+    ([300] * 8, 2048, True, False, 192),          # 256 tiles, one round
+    ([150] * 32, 2048, True, False, 192),
+    ([384] * 64, 1408, True, False, 192)])
+def test_tall_height_of_a_pass(counts, n_cols, gateup, fp8, want):
+    assert R.tall_height(counts, n_cols, gateup, fp8) == want
