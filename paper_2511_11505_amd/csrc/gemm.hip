@@ -1408,13 +1408,12 @@ hipError_t launch_grouped_ffn(int dtype, int G, int ffn, int d, const void* in,
     } else if (kind == PASS_RING) {
       const int v = tile_choice(!gateup, NOUT);
       KSplit sp;
-      if (v == 5)
+      if (v == 5 && ring_may_split(G, K))
         sp = make_split(ring_splits(gateup, 128, max_rows, G, K / 64, NOUT, pbytes), K / 64, P);
       gemm_pass<MODE>(v, (const bf16_t*)a, rows, goff, G, max_rows, (const bf16_t*)w, K, NOUT,
                       (bf16_t*)c, NOUT, s, sp);
       reduce_split<MODE>(sp, rows, goff, G, max_rows, NOUT, (bf16_t*)c, NOUT, s);
-    } else if (!gateup && G == 1 && max_rows <= 64 && K % 512 == 0 && NOUT % 32 == 0) {
-      // one group of at most 64 rows: the skinny down pass where K allows it
+    } else if (kind == PASS_SKINNY) {
       launch_k(gemm_bf16_skinny_down_kernel, (unsigned)(NOUT / 32), 256, 0, s, (const bf16_t*)a, rows,
                goff, max_rows, (const bf16_t*)w, K, NOUT, (bf16_t*)c, NOUT);
     } else {

@@ -24,9 +24,15 @@ inline bool use_stream(int dtype, int64_t max_rows, int G, int ffn, int d) {
   return ring_tiles < 256;
 }
 
+// Relative time of one dense group on tiles of up to h rows: rounds of tiles over
+// the CUs, each costing its rows and a fixed part worth about 32.
+inline int64_t r192_cost(int64_t rows, int n_tiles, int cus, int h, int unit) {
+  const int64_t t = cdiv(rows, h), height = cdiv(cdiv(rows, t), unit) * unit;
+  return cdiv(t * n_tiles, cus) * (height + 32);
+}
+
 // Largest tile height of a pass on the 192-row tiles.  Of one dense group,
-// whose rows the host knows: the height whose rounds of tiles over the CUs
-// (each costing its rows, and a fixed part worth about 32) are shortest.
+// whose rows the host knows: the one of least cost.
 // Of routed groups, whose sizes are known on the device only, 0: the kernel
 // chooses (tall_tiles.hpp), in about 0.5 us; but 192 where the rows make four
 // rounds of 128-row tiles and more, since the height then matters little: of 57
@@ -34,16 +40,23 @@ inline bool use_stream(int dtype, int64_t max_rows, int G, int ffn, int d) {
 inline int r192_height(int64_t max_rows, int G, int n_tiles, int cus, int unit = 32) {
   if (G > 1) return max_rows * n_tiles >= (int64_t)4 * 128 * cus ? 192 : 0;
   int best = 192;
-  int64_t best_cost = -1;
-  for (int h = 192; h >= 128; h -= unit) {
-    const int64_t t = cdiv(max_rows, h), height = cdiv(cdiv(max_rows, t), unit) * unit;
-    const int64_t cost = cdiv(t * n_tiles, cus) * (height + 32);
-    if (best_cost < 0 || cost < best_cost) {
-      best_cost = cost;
-      best = h;
-    }
-  }
+  for (int h = 192 - unit; h >= 128; h -= unit)
+    if (r192_cost(max_rows, n_tiles, cus, h, unit) < r192_cost(max_rows, n_tiles, cus, best, unit)) best = h;
   return best;
+}
+
+// Whether the 192-row tiles pay on one dense group.  Yes where a height above
+// 128 saves rounds: 68 bf16 passes of 700 to 4096 rows took 0.61 to 0.92 of the
+// ring's time.  At 128 rows both kernels run the same tiles, and the ring's
+// eight waves are the better ones on few m-tiles (d 5120, F 8192, gate/up of 1000
+// rows: 149 us, 155 here; 2048 rows 285 and 284) and where the last round leaves
+// more than a fifth of the CUs idle (d 3072, F 1536, 4096 rows, 384 tiles: 79 +
+// 47 us, 84 + 51 here).
+inline bool r192_pays(int64_t rows, int n_tiles, int cus, int unit = 32) {
+  const int64_t ring = cdiv(rows, 128) * n_tiles, rounds = cdiv(ring, cus);
+  const int h = r192_height(rows, 1, n_tiles, cus, unit);
+  if (r192_cost(rows, n_tiles, cus, h, unit) < rounds * (128 + 32)) return true;
+  return rows > 1024 && ring * 5 >= rounds * cus * 4;
 }
 
 // The 192-row tiles take the passes whose groups average at least 112 rows and
@@ -62,7 +75,43 @@ inline bool r192_ok(int64_t rows, int G, int k_blocks, int64_t ring_tiles, int c
 }
 
 // Kernel of one pass (gate/up: NOUT = F, K = d; down: NOUT = d, K = F).
-enum PassKind { PASS_R64, PASS_STREAM, PASS_RING, PASS_R192 };
+enum PassKind { PASS_R64, PASS_STREAM, PASS_RING, PASS_R192, PASS_SKINNY };
+
+// One dense group whose 128 x 256 ring tiles leave CUs idle, K below 4096: the
+// 64-row tiles while they make one round (two of 64 x 128 fit a CU), from there
+// the ring, in one round and without a K split.  (us, 64-row tiles | ring | ring
+// with K split and the reduction) gate/up of d 2048, F 2816 (K 2048): 333 rows
+// 20 | 30 | 40, 700 rows (484 tiles) 28 | 29 | 49, 1000 rows (704) 40 | 30 | 44,
+// 1400 rows 52 | 32 | 59; down of d 7168, F 2048: 333 rows 28 | 31 | 45, 700
+// rows (616) 43 | 31 | 51; linear, n 5120: K 640, 640 rows (400) 10.5 | 13.2,
+// 1300 rows (840) 17.5 | 15.0; K 384, 1300 rows 14.1 | 12.6.  A longer K needs
+// the split: gate/up of d 7168, F 2048, 64 rows 35 | 91 | 24.  Columns that the
+// 256-wide tiles do not divide have 128 x 128 ring tiles, twice as many: to one
+// 64-row tile per CU (linear, n 1152, K 1024: 1700 rows, 243 tiles 12.0 | 12.7,
+// 2000 rows, 288 tiles 13.7 | 12.9).
+inline bool r64_one_round(int64_t rows, int n_wide, int K, int cus, bool ring256) {
+  return K < 4096 && cdiv(rows, 64) * n_wide <= (ring256 ? 2 : 1) * cus;
+}
+// The ring splits K where its tiles leave CUs idle, but not as above.
+inline bool ring_may_split(int G, int K) { return G > 1 || K >= 4096; }
+
+// One dense group of at most 64 rows.  Whole K per workgroup, no reduction:
+// - down passes of very few rows: 32 output columns per workgroup, K cut over
+//   its waves (the skinny kernel; K % 512 == 0).  us, skinny and 64-row tiles: d
+//   7168, F 2048, 1 row 8.7 and 10.2, 20 rows 10.8 and 11.2, 33 rows 12.0 and
+//   11.9; d 1024, F 512, 48 rows 5.2 and 5.7; d 5120, F 8192, 8 rows 28.1 and
+//   29.2, 20 rows 33.0 and 31.2;
+// - the 64-row tiles while their narrow weight tiles occupy enough CUs for the
+//   length of K.  us, 64-row tiles and streaming: gate/up of d 2048, F 2816, 1
+//   row 10.2 and 12.8; d 5120, F 8192, 64 rows 34 and 53 (256 tiles); but d
+//   3072, F 1536, 1 row 12.8 and 12.1, 20 rows 15.7 and 14.2, 33 rows 15.7 and
+//   16.3 (48 tiles), and d 7168, F 2048, 1 row 24.8 and 18.0, 64 rows 35 and 25;
+// else weight streaming.
+inline PassKind few_rows_kind(bool gateup, int64_t rows, int NOUT, int K) {
+  const int64_t narrow = NOUT / (gateup ? 32 : 64);
+  if (!gateup && K % 512 == 0 && (rows <= 8 || rows * K <= 40960)) return PASS_SKINNY;
+  return K < 2560 || narrow * 50 >= K || (rows > 32 && K < 4096) ? PASS_R64 : PASS_STREAM;
+}
 
 // The 64-row tiles (gemm_r64.hip) take fp32, widths the ring's tiles do not
 // divide, and, of the bf16 passes that others could take as well:
@@ -71,48 +120,42 @@ enum PassKind { PASS_R64, PASS_STREAM, PASS_RING, PASS_R192 };
 //   + down: 6 rows a group 146 + 68 us on the ring, 137 + 65 us on 64-row
 //   tiles; 31 rows 160 + 71 and 148 + 70; but 66 rows 169 + 76 and 177 + 95,
 //   and 32 groups of 16 rows, d 7168, F 2048: 295 + 163 and 301 + 179;
-// - one dense group whose 128 x 256 ring tiles would leave CUs idle and K be
-//   split, for K below 4096 (us with the split and its reduction -> on 64-row
-//   tiles): d 2048, F 2816, gate/up + down, 333 rows 42 + 24 -> 22 + 16, 1365
-//   rows 64 + 60 -> 58 + 38; down of d 7168, F 2048: 64 rows 18 -> 16, 333
-//   rows 52 -> 34, 1000 rows 69 -> 62.  A long K needs the split: gate/up of
-//   that shape, 64 rows 30 -> 41, 1000 rows 135 -> 141;
-// - unless the rows fit one tile and the weight tiles alone occupy enough CUs
-//   (more than a quarter): d 5120, F 8192, 64 rows: gate/up 60 -> 39 (256
-//   tiles), down 59 -> 43 (80 tiles).
+// - one dense group as above.
 inline PassKind pass_kind(int dtype, bool gateup, int64_t max_rows, int64_t likely_rows, int G,
                           int ffn, int d, int cus) {
   if (dtype != 1) return PASS_R64;
-  const int NOUT = gateup ? ffn : d, K = gateup ? d : ffn;
+  const int NOUT = gateup ? ffn : d, K = gateup ? d : ffn, n_tiles = NOUT / (gateup ? 128 : 256);
   const bool stream = use_stream(dtype, max_rows, G, ffn, d);
   if (G == 1) {
-    const int64_t ring_tiles = cdiv(max_rows, 128) * (NOUT / (gateup ? 128 : 256));
-    if (ring_tiles < cus &&
-        (K < 4096 || (max_rows <= 64 && NOUT / (gateup ? 32 : 64) > cus / 4)))
-      return PASS_R64;
+    if (stream) return few_rows_kind(gateup, max_rows, NOUT, K);
+    if (r64_one_round(max_rows, NOUT / (gateup ? 64 : 128), K, cus, gateup || d % 256 == 0)) return PASS_R64;
   } else if (!stream && max_rows <= (int64_t)48 * G && d < 4096) {
     return PASS_R64;
   }
   if (stream) return PASS_STREAM;
   if (ffn % 128 != 0 || d % 256 != 0) return PASS_R64;
-  const int64_t ring_tiles = G * cdiv(max_rows, (int64_t)128 * G) * (NOUT / (gateup ? 128 : 256));
-  return r192_ok(likely_rows, G, K / 64, ring_tiles, cus) ? PASS_R192 : PASS_RING;
+  const int64_t ring_tiles = G * cdiv(max_rows, (int64_t)128 * G) * n_tiles;
+  if (!r192_ok(likely_rows, G, K / 64, ring_tiles, cus)) return PASS_RING;
+  return G > 1 || r192_pays(max_rows, n_tiles, cus) ? PASS_R192 : PASS_RING;
 }
 
 // An FP8 pass: the ring or the 192-row tiles.
 inline PassKind pass_kind_fp8(bool gateup, int64_t max_rows, int G, int ffn, int d, int cus) {
-  const int NOUT = gateup ? ffn : d, K = gateup ? d : ffn;
-  const int64_t ring_tiles = G * cdiv(max_rows, (int64_t)128 * G) * (NOUT / (gateup ? 128 : 256));
-  return r192_ok(max_rows, G, K / 128, ring_tiles, cus) ? PASS_R192 : PASS_RING;
+  const int NOUT = gateup ? ffn : d, K = gateup ? d : ffn, n_tiles = NOUT / (gateup ? 128 : 256);
+  const int64_t ring_tiles = G * cdiv(max_rows, (int64_t)128 * G) * n_tiles;
+  if (!r192_ok(max_rows, G, K / 128, ring_tiles, cus)) return PASS_RING;
+  return G > 1 || r192_pays(max_rows, n_tiles, cus, 64) ? PASS_R192 : PASS_RING;
 }
 
 // A dense linear, one group of m rows: 64-row tiles where the ring's would
-// leave CUs idle (as pass_kind), else the 192-row tiles, else the ring (128 x
-// 128 tiles when n is not a multiple of 256).
+// leave CUs idle (as above), else the 192-row tiles, else the ring (128 x 128
+// tiles when n is not a multiple of 256; never split).
 inline PassKind dense_kind(int dtype, int m, int n, int kdim, int cus) {
+  if (dtype != 1 || r64_one_round(m, n / 128, kdim, cus, n % 256 == 0)) return PASS_R64;
   const int64_t ring_tiles = cdiv(m, 128) * (n / (n % 256 == 0 ? 256 : 128));
-  if (dtype != 1 || (ring_tiles < cus && kdim < 4096)) return PASS_R64;
-  return n % 256 == 0 && r192_ok(m, 1, kdim / 64, ring_tiles, cus) ? PASS_R192 : PASS_RING;
+  return n % 256 == 0 && r192_ok(m, 1, kdim / 64, ring_tiles, cus) && r192_pays(m, n / 256, cus)
+             ? PASS_R192
+             : PASS_RING;
 }
 
 // Tile variant of the LDS-ring GEMMs, per pass: the interleaved 128 x 256

@@ -12,6 +12,7 @@ import torch
 import oracle
 from paper_2511_11505_amd import _lib as L
 from paper_2511_11505_amd.block import fragment_ordered_fp8
+from tests import _rules as R
 from tests._util import TOL, f64, rel_err
 from workloads import CONFIGS
 
@@ -77,6 +78,27 @@ def test_ffn_edges(dtype, counts, d, F, gather, slack):
     check_ffn(dtype, X, rows, goff, wgu, wd, out)
 
 
+# one dense group on every route its rules lead to (asserted): few rows on the
+# skinny, streaming and 64-row kernels, the ring in one round without a K split,
+# the ring and the 192-row tiles at equal heights
+@pytest.mark.parametrize("rows,d,F,gu,dn", [
+    (1, 3072, 1536, R.STREAM, R.SKINNY), (20, 3072, 1536, R.STREAM, R.SKINNY),
+    (8, 512, 5120, R.R64, R.SKINNY), (40, 512, 1024, R.R64, R.SKINNY), (50, 1024, 512, R.R64, R.SKINNY),
+    (64, 4096, 1024, R.STREAM, R.R64), (1, 2048, 2816, R.R64, R.STREAM), (33, 3072, 1408, R.R64, R.R64),
+    (700, 2048, 2816, R.R64, R.R64), (1100, 2048, 2816, R.RING, R.R64), (1000, 5120, 384, R.RING, R.RING),
+    (1000, 768, 8192, R.RING, R.RING), (4096, 256, 768, R.RING, R.R64)])
+def test_dense_group_routes(rows, d, F, gu, dn):
+    assert (R.pass_kind(True, rows, 1, F, d), R.pass_kind(False, rows, 1, F, d)) == (gu, dn)
+    X, _, goff, wgu, wd, n_src = ffn_case("bf16", [rows], d, F, False, seed=3)
+    out = torch.full((n_src, d), float("nan"), device=DEV).to(torch.bfloat16)
+    desc = L.make_desc(CONFIGS["tiny"].scaled(hidden=d, ffn=F, dtype="bf16"))
+    ws = torch.empty((L.fs_workspace_size(desc, L.FS_OP_GROUPED_FFN, rows, F),), dtype=torch.uint8,
+                     device=DEV)
+    L.fs_grouped_expert_ffn(desc, 1, F, X, None, None, rows, wgu, wd, out, ws)
+    torch.cuda.synchronize()
+    check_ffn("bf16", X, None, goff, wgu, wd, out)
+
+
 # 192-row tiles: every tile height (128 to 192 in steps of 32 and the short
 # tiles below) and every largest height that a pass may choose (160, 192, 128),
 # groups of one to several equal tiles, one band and more of m-tiles, several
@@ -103,7 +125,8 @@ def test_ffn_tall_tiles(counts, d, F, gather, slack):
 
 @pytest.mark.parametrize("dtype,m,n,kd", [
     ("bf16", 2300, 3840, 256), ("bf16", 4097, 2048, 384), ("f32", 1, 64, 64), ("f32", 65, 192, 128), ("f32", 129, 4096, 320), ("f32", 1030, 8256, 64),
-    ("bf16", 33, 640, 4032), ("bf16", 130, 384, 4096), ("bf16", 1000, 2048, 192)])
+    ("bf16", 33, 640, 4032), ("bf16", 130, 384, 4096), ("bf16", 1000, 2048, 192),
+    ("bf16", 2000, 1152, 320), ("bf16", 1300, 5120, 64)])
 def test_dense_linear_edges(dtype, m, n, kd):
     gen = torch.Generator(device=DEV).manual_seed(m + n)
     a = torch.randn((m, kd), generator=gen, device=DEV).to(TORCH[dtype])

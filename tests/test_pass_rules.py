@@ -29,6 +29,8 @@ def test_pass_kernels_take_their_widths(gateup):
             assert rows <= min(64 * G, 4096) and n % 64 == 0 and K % 64 == 0
         elif kind == R.RING:
             assert n % (128 if gateup else 256) == 0 and K % 64 == 0
+        elif kind == R.SKINNY:
+            assert not gateup and G == 1 and rows <= 64 and K % 512 == 0 and n % 32 == 0
         else:
             assert kind == R.R192 and n % (128 if gateup else 256) == 0 and K % 64 == 0 and K >= 256
         if ffn % 128 == 0 and d % 256 == 0:
@@ -76,3 +78,27 @@ def test_tall_order_visits_every_tile_in_bands():
     ([384] * 64, 1408, True, False, 192)])
 def test_tall_height_of_a_pass(counts, n_cols, gateup, fp8, want):
     assert R.tall_height(counts, n_cols, gateup, fp8) == want
+
+
+# one dense group on both sides of each line, named by (rows, d, F)
+@pytest.mark.parametrize("gateup,rows,d,F,kind", [
+    (True, 700, 2048, 2816, R.R64), (True, 1000, 2048, 2816, R.RING),      # 484 and 704 tiles of 64 rows
+    (False, 640, 5120, 384, R.R64), (False, 1000, 5120, 384, R.RING),
+    (False, 1, 7168, 2048, R.SKINNY), (False, 33, 7168, 2048, R.R64),
+    (False, 8, 5120, 8192, R.SKINNY), (False, 50, 1024, 512, R.SKINNY),
+    (True, 1, 3072, 1536, R.STREAM), (True, 33, 3072, 1536, R.R64),
+    (True, 1, 2048, 2816, R.R64), (True, 64, 7168, 2048, R.STREAM), (True, 64, 5120, 8192, R.R64),
+    (False, 1, 2048, 2816, R.STREAM),
+    (False, 4096, 3072, 1536, R.RING), (True, 4096, 3072, 1536, R.RING),   # 384 tiles, 128 rows high
+    (True, 1000, 5120, 8192, R.RING), (True, 2048, 5120, 8192, R.R192),
+    (True, 1400, 5120, 8192, R.R192)])
+def test_dense_group_routes(gateup, rows, d, F, kind):
+    assert R.pass_kind(gateup, rows, 1, F, d) == kind
+
+
+@pytest.mark.parametrize("m,n,k,kind", [
+    (640, 5120, 640, R.R64), (800, 5120, 640, R.RING), (1300, 5120, 640, R.RING),
+    (1300, 5120, 384, R.RING), (1700, 5120, 640, R.R192), (2400, 2048, 2048, R.RING),
+    (1300, 4096, 3072, R.RING), (4096, 3072, 3072, R.RING), (1700, 1152, 1024, R.R64), (2000, 1152, 1024, R.RING)])
+def test_dense_linear_routes(m, n, k, kind):
+    assert R.dense_kind(m, n, k) == kind
