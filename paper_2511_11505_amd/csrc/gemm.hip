@@ -29,6 +29,177 @@
 namespace fs {
 namespace {
 
+// ---------------------------------------------------------------- bf16 MFMA, register-staged
+// BM x BN x BK tiles through registers and double-buffered LDS, for gate/up
+// (and some down) passes whose columns the ring's 256-wide tiles do not divide:
+// 128 x 128 tiles, two workgroups per CU.  24 groups of 108 rows, d 1408, F 960,
+// gate/up + down: 65 us, on the 64-row tiles 73; 64 groups of 300 rows, d 1664,
+// F 2496: 770 and 856.
+template <int MODE, int BM, int BN, int BK, int WAVES_M, int WAVES_N>
+__global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_kernel(
+    const bf16_t* __restrict__ A, const int32_t* __restrict__ rows,
+    const int32_t* __restrict__ goff, int G, int64_t m_total, const bf16_t* __restrict__ B, int K,
+    int NOUT, bf16_t* __restrict__ C, int ldc) {
+  constexpr int NT = 64 * WAVES_M * WAVES_N;
+  constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N;
+  constexpr int TM = WTM / 32, TN = WTN / 32;
+  constexpr int LDK = BK + 8;  // LDS row stride in bf16: 16-byte skew per row
+  constexpr int CPR = BK / 8;  // 16-byte chunks per tile row
+  constexpr int ACH = BM * CPR / NT, BCH = BN * CPR / NT;
+  constexpr int NCOL = (MODE == MODE_GATEUP) ? BN / 2 : BN;
+  constexpr int STAGE = (BM + BN) * LDK;
+  static_assert(BM * CPR % NT == 0 && BN * CPR % NT == 0, "tile loads must divide evenly");
+  static_assert(MODE != MODE_GATEUP || TN % 2 == 0, "gate/up tiles come in pairs");
+
+  __shared__ int s_goff[kMaxGroups + 1];
+  __shared__ int s_tpre[kMaxGroups + 1];
+  __shared__ int s_wtot[NT / 64];
+  __shared__ __align__(16) bf16_t lds[2 * STAGE];
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave / WAVES_N, wn = wave % WAVES_N;
+  sched_setup<NT, BM>(goff, G, m_total, s_goff, s_tpre, s_wtot);
+
+  const int nn = NOUT / NCOL;
+  const int64_t total = (int64_t)nn * s_tpre[G];
+  const int64_t per_xcd = (total + kXcd - 1) / kXcd;
+  const int64_t xcd_base = (int64_t)(blockIdx.x % kXcd) * per_xcd;
+  const int64_t stride = gridDim.x / kXcd;
+  const int KT = K / BK;
+  const size_t bstride = (size_t)((MODE == MODE_GATEUP) ? 2 * NOUT : NOUT) * K;
+
+  for (int64_t j = blockIdx.x / kXcd; j < per_xcd; j += stride) {
+    const int64_t L = xcd_base + j;
+    if (L >= total) break;
+    const int g = find_group(s_tpre, G, nn, L);
+    const int Tg = s_tpre[g + 1] - s_tpre[g];
+    const int64_t local = L - (int64_t)nn * s_tpre[g];
+    const int nt = (int)(local / Tg), mt = (int)(local % Tg);
+    const int row_base = s_goff[g], rows_g = s_goff[g + 1] - row_base;
+    const int m0 = mt * BM, n0 = nt * NCOL;
+    const bf16_t* Bg = B + (size_t)g * bstride;
+
+    const bf16_t* pa[ACH];
+    bool va[ACH];
+#pragma unroll
+    for (int i = 0; i < ACH; ++i) {
+      const int c = tid + i * NT;
+      const int r = c / CPR, kc = (c % CPR) * 8;
+      const int m = m0 + r;
+      va[i] = m < rows_g;
+      const int grow = row_base + (va[i] ? m : 0);
+      const int64_t src = (MODE == MODE_GATEUP && rows) ? (int64_t)rows[grow] : (int64_t)grow;
+      pa[i] = A + src * K + kc;
+    }
+    const bf16_t* pb[BCH];
+#pragma unroll
+    for (int i = 0; i < BCH; ++i) {
+      const int c = tid + i * NT;
+      const int r = c / CPR, kc = (c % CPR) * 8;
+      int wrow;
+      if (MODE == MODE_GATEUP)
+        wrow = (r < BN / 2) ? n0 + r : NOUT + n0 + (r - BN / 2);
+      else
+        wrow = n0 + r;
+      pb[i] = Bg + (size_t)wrow * K + kc;
+    }
+
+    floatx16 acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int jn = 0; jn < TN; ++jn)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[i][jn][v] = 0.f;
+
+    uint4 ra[ACH], rb[BCH];
+    auto gload = [&](int k0) {
+#pragma unroll
+      for (int i = 0; i < ACH; ++i) ra[i] = va[i] ? ld16(pa[i] + k0) : make_uint4(0, 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < BCH; ++i) rb[i] = ld16(pb[i] + k0);
+    };
+    auto lstore = [&](int buf) {
+      bf16_t* As = lds + buf * STAGE;
+      bf16_t* Bs = As + BM * LDK;
+#pragma unroll
+      for (int i = 0; i < ACH; ++i) {
+        const int c = tid + i * NT;
+        st16(As + (c / CPR) * LDK + (c % CPR) * 8, ra[i]);
+      }
+#pragma unroll
+      for (int i = 0; i < BCH; ++i) {
+        const int c = tid + i * NT;
+        st16(Bs + (c / CPR) * LDK + (c % CPR) * 8, rb[i]);
+      }
+    };
+
+    gload(0);
+    for (int kt = 0; kt < KT; ++kt) {
+      lstore(kt & 1);
+      __syncthreads();
+      if (kt + 1 < KT) gload((kt + 1) * BK);
+      const bf16_t* As = lds + (kt & 1) * STAGE;
+      const bf16_t* Bs = As + BM * LDK;
+#pragma unroll
+      for (int ks = 0; ks < BK / 16; ++ks) {
+        const int kofs = ks * 16 + (lane >> 5) * 8;
+        bf16x8 af[TM], bfr[TN];
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+          const int r = wm * WTM + i * 32 + (lane & 31);
+          af[i] = *reinterpret_cast<const bf16x8*>(As + r * LDK + kofs);
+        }
+#pragma unroll
+        for (int jn = 0; jn < TN; ++jn) {
+          int br;
+          if (MODE == MODE_GATEUP)
+            br = (jn < TN / 2) ? wn * (WTN / 2) + jn * 32
+                               : BN / 2 + wn * (WTN / 2) + (jn - TN / 2) * 32;
+          else
+            br = wn * WTN + jn * 32;
+          bfr[jn] = *reinterpret_cast<const bf16x8*>(Bs + (br + (lane & 31)) * LDK + kofs);
+        }
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int jn = 0; jn < TN; ++jn)
+            acc[i][jn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], bfr[jn], acc[i][jn], 0,
+                                                                 0, 0);
+      }
+    }
+
+    // Epilogue.  Accumulator element v of lane l holds row
+    // 8*(v/4) + 4*(l/32) + v%4 and column l%32 of its 32x32 tile.
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int m = m0 + wm * WTM + i * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+        if (m >= rows_g) continue;
+        const int grow = row_base + m;
+        if (MODE == MODE_GATEUP) {
+#pragma unroll
+          for (int jn = 0; jn < TN / 2; ++jn) {
+            const float gt = acc[i][jn][v], up = acc[i][jn + TN / 2][v];
+            const float h = swiglu_bf16_epi(gt, up);
+            const int col = n0 + wn * (WTN / 2) + jn * 32 + (lane & 31);
+            C[(size_t)grow * ldc + col] = f2bf(h);
+          }
+        } else {
+          const int64_t orow = rows ? (int64_t)rows[grow] : (int64_t)grow;
+#pragma unroll
+          for (int jn = 0; jn < TN; ++jn) {
+            const int col = n0 + wn * WTN + jn * 32 + (lane & 31);
+            C[orow * ldc + col] = f2bf(acc[i][jn][v]);
+          }
+        }
+      }
+    }
+    __syncthreads();  // LDS stages are reused by the next tile
+  }
+}
+
 // ---------------------------------------------------------------- bf16 MFMA, DMA ring
 // BM x BN x 64 tiles, four waves (2 x 2), each wave BM/2 x BN/2 through
 // v_mfma_f32_32x32x16_bf16.  Operand tiles stream into an LDS ring of
@@ -1174,6 +1345,26 @@ int num_cus() {
   return cus;
 }
 
+// The ring's tiles: 128 x 256 x 64 with eight waves; 128 x 128 with four for
+// output widths that are a multiple of 128 but not of 256.
+// Measured against it and dropped (block steps, same box):
+// - a register-staged 256 x 256 kernel on dense gate/up (Llama-4-Scout-shaped
+//   shared expert 1317 -> 1232 us for the ring);
+// - 256-row tiles on routed passes, whose half-empty tail tiles waste MFMA
+//   work;
+// - 256 x 256 tiles (eight waves of 128 x 64, two 64 KB slots, 16 x 16 x 32
+//   MFMAs) on dense passes.  Alone they are faster on the DeepSeek-V3-shaped
+//   shared expert (gate/up 195 -> 184 us, down 119 -> 111 us), but their
+//   workgroups hold a whole CU's registers, and in the block, where the
+//   shared passes run beside the Dispatch stand-in copy, the copy's cost
+//   moves to whichever pass it overlaps: gate/up alone on them, 380 -> 230
+//   us, shared down 133 -> 399 us, step 3.78 -> 3.93 ms.  Llama-4-Scout-shaped
+//   shared gate/up (eight rounds of tiles) 1215 -> 1402 us;
+// - two K groups of four waves on the 128 x 256 tile (each wave 64 x 128
+//   over every other 32-wide K step, partial sums added in LDS): a quarter
+//   fewer LDS fragment reads, yet Llama-4-Scout-shaped routed gate/up 1390
+//   -> 1408 us, DeepSeek-V3-shaped down 977 -> 1050 us.
+
 // occ workgroups per compute unit (capped by the tile count, a multiple of 8).
 int64_t persistent_grid(int64_t max_rows, int G, int BM, int nn, int occ) {
   const int cus = num_cus();
@@ -1228,23 +1419,18 @@ void run_il_f8(const uint8_t* A, const int32_t* rows, const int32_t* goff, int G
              64 * WGM * WGN, 0, s, A, rows, goff, G, m_total, B, K, NOUT, C, ldc, sA, sB, 1, K / 128,
              nullptr);
 }
-// Variant 5 has BN = 256 and BK = 64: it needs NOUT % 128 == 0 for
-// gate/up, NOUT % 256 == 0 for down and K % 64 == 0.  Variant 10 (down
-// only) has 128 x 128 tiles for NOUT % 128 == 0.  (A K split applies to
-// variant 5 only.)
+// One bf16 pass on the ring: 128 x 256 tiles (NOUT % 128 == 0 for gate/up, % 256
+// == 0 for down, K % 64 == 0; sp may split K) or, down only, 128 x 128 tiles of
+// four waves in four 32 KB slots (NOUT % 128 == 0).
 template <int MODE>
-void gemm_pass(int v, const bf16_t* A, const int32_t* rows, const int32_t* goff, int G,
-               int64_t m_total, const bf16_t* B, int K, int NOUT, bf16_t* C, int ldc,
-               hipStream_t s, const KSplit& sp = KSplit{}) {
-#define FS_ARGS A, rows, goff, G, m_total, B, K, NOUT, C, ldc, s
-  switch (v) {
-    case 10:
-      // 128 x 128 tiles, four waves of 64 x 64, four 32 KB slots
-      if constexpr (MODE == MODE_DOWN) run_il<MODE, 128, 128, 64, 4, 1>(FS_ARGS);
-      break;
-    default: run_il<MODE, 128, 256, 64, 3, 1, 2, 4, true>(FS_ARGS, sp); break;   // 5
-  }
-#undef FS_ARGS
+void gemm_pass(const bf16_t* A, const int32_t* rows, const int32_t* goff, int G, int64_t m_total,
+               const bf16_t* B, int K, int NOUT, bf16_t* C, int ldc, hipStream_t s,
+               const KSplit& sp = KSplit{}) {
+  run_il<MODE, 128, 256, 64, 3, 1, 2, 4, true>(A, rows, goff, G, m_total, B, K, NOUT, C, ldc, s, sp);
+}
+void down_pass_128(const bf16_t* A, const int32_t* rows, const int32_t* goff, int G, int64_t m_total,
+                   const bf16_t* B, int K, int NOUT, bf16_t* C, hipStream_t s) {
+  run_il<MODE_DOWN, 128, 128, 64, 4, 1>(A, rows, goff, G, m_total, B, K, NOUT, C, NOUT, s);
 }
 
 }  // namespace
@@ -1405,14 +1591,19 @@ hipError_t launch_grouped_ffn(int dtype, int G, int ffn, int d, const void* in,
       const int hmax = r192_height(likely_rows, G, NOUT / (gateup ? 128 : 256), num_cus());
       (gateup ? launch_r192_gateup : launch_r192_down)(a, rows, goff, G, max_rows, w, K, NOUT, c, NOUT,
                                                        num_cus(), hmax, s);
+    } else if (kind == PASS_STAGED) {
+      launch_k(gemm_bf16_kernel<MODE, 128, 128, 64, 2, 2>,
+               (unsigned)grid_for(max_rows, G, 128, NOUT / (gateup ? 64 : 128)), 256, 0, s,
+               (const bf16_t*)a, rows, goff, G, max_rows, (const bf16_t*)w, K, NOUT, (bf16_t*)c, NOUT);
     } else if (kind == PASS_RING) {
-      const int v = tile_choice(!gateup, NOUT);
       KSplit sp;
-      if (v == 5 && ring_may_split(G, K))
+      if (ring_may_split(G, K))
         sp = make_split(ring_splits(gateup, 128, max_rows, G, K / 64, NOUT, pbytes), K / 64, P);
-      gemm_pass<MODE>(v, (const bf16_t*)a, rows, goff, G, max_rows, (const bf16_t*)w, K, NOUT,
-                      (bf16_t*)c, NOUT, s, sp);
+      gemm_pass<MODE>((const bf16_t*)a, rows, goff, G, max_rows, (const bf16_t*)w, K, NOUT, (bf16_t*)c,
+                      NOUT, s, sp);
       reduce_split<MODE>(sp, rows, goff, G, max_rows, NOUT, (bf16_t*)c, NOUT, s);
+    } else if (kind == PASS_RING128) {
+      down_pass_128((const bf16_t*)a, rows, goff, G, max_rows, (const bf16_t*)w, K, NOUT, (bf16_t*)c, s);
     } else if (kind == PASS_SKINNY) {
       launch_k(gemm_bf16_skinny_down_kernel, (unsigned)(NOUT / 32), 256, 0, s, (const bf16_t*)a, rows,
                goff, max_rows, (const bf16_t*)w, K, NOUT, (bf16_t*)c, NOUT);
@@ -1530,9 +1721,11 @@ hipError_t launch_dense_linear(int dtype, int m, int n, int kdim, const void* a,
   else if (kind == PASS_R192)
     launch_r192_down(a, nullptr, nullptr, 1, m, w, kdim, n, out, n, num_cus(),
                      r192_height(m, 1, n / 256, num_cus()), s);
+  else if (kind == PASS_RING128)
+    down_pass_128((const bf16_t*)a, nullptr, nullptr, 1, m, (const bf16_t*)w, kdim, n, (bf16_t*)out, s);
   else
-    gemm_pass<MODE_DOWN>(tile_choice(true, n), (const bf16_t*)a, nullptr, nullptr, 1,
-                         m, (const bf16_t*)w, kdim, n, (bf16_t*)out, n, s);
+    gemm_pass<MODE_DOWN>((const bf16_t*)a, nullptr, nullptr, 1, m, (const bf16_t*)w, kdim, n,
+                         (bf16_t*)out, n, s);
   return hipGetLastError();
 }
 

@@ -75,7 +75,8 @@ inline bool r192_ok(int64_t rows, int G, int k_blocks, int64_t ring_tiles, int c
 }
 
 // Kernel of one pass (gate/up: NOUT = F, K = d; down: NOUT = d, K = F).
-enum PassKind { PASS_R64, PASS_STREAM, PASS_RING, PASS_R192, PASS_SKINNY };
+// RING128: the ring's 128 x 128 tiles, for down passes and linears.
+enum PassKind { PASS_R64, PASS_STREAM, PASS_RING, PASS_R192, PASS_SKINNY, PASS_STAGED, PASS_RING128 };
 
 // One dense group whose 128 x 256 ring tiles leave CUs idle, K below 4096: the
 // 64-row tiles while they make one round (two of 64 x 128 fit a CU), from there
@@ -89,7 +90,7 @@ enum PassKind { PASS_R64, PASS_STREAM, PASS_RING, PASS_R192, PASS_SKINNY };
 // 256-wide tiles do not divide have 128 x 128 ring tiles, twice as many: to one
 // 64-row tile per CU (linear, n 1152, K 1024: 1700 rows, 243 tiles 12.0 | 12.7,
 // 2000 rows, 288 tiles 13.7 | 12.9).
-inline bool r64_one_round(int64_t rows, int n_wide, int K, int cus, bool ring256) {
+inline bool r64_one_round(int64_t rows, int n_wide, int K, int cus, bool ring256 = true) {
   return K < 4096 && cdiv(rows, 64) * n_wide <= (ring256 ? 2 : 1) * cus;
 }
 // The ring splits K where its tiles leave CUs idle, but not as above.
@@ -113,8 +114,38 @@ inline PassKind few_rows_kind(bool gateup, int64_t rows, int NOUT, int K) {
   return K < 2560 || narrow * 50 >= K || (rows > 32 && K < 4096) ? PASS_R64 : PASS_STREAM;
 }
 
-// The 64-row tiles (gemm_r64.hip) take fp32, widths the ring's tiles do not
-// divide, and, of the bf16 passes that others could take as well:
+// A pass whose columns the ring's 256-wide tiles do not divide (gate/up F % 128 =
+// 64, down d % 256 = 128).  All of them can run on 64-row tiles; long passes are
+// faster on 128-row ones: gate/up on the register-staged 128 x 128 tiles, whose
+// rounds (two workgroups per CU, as of the 64-row tiles) take about 1.35 times
+// as long, down on the ring's 128 x 128 tiles (one per CU).
+// us, 64-row | staged | ring 128 x 128 tiles: gate/up of 64 groups of 110 rows, d
+// 1664, F 2496: 294 | 252 | 268; of 16 groups of 180 rows, d 640, F 1472: 28 | 32 |
+// 32; down of the first 166 | 133 | 131, of the second 18 | 32 | 22; down of 3000
+// rows in one group, d 4480, F 1536: 65 | 66 | 62, 1500 rows 38 | 33 | 37 (420 ring
+// tiles: two rounds on the ring, one staged), 700 rows 23 | 28 | 18.
+// Group sizes are known on the device only: a group of r rows is taken to make
+// r / 128 + 0.4 tiles, at least one.
+inline PassKind odd_kind(bool gateup, int64_t rows, int G, int NOUT, int cus) {
+  const int64_t n = NOUT / (gateup ? 64 : 128), slots = 2 * cus;
+  if (gateup) {
+    auto rounds = [&](int64_t bm) {
+      const int64_t tiles = G == 1 ? cdiv(rows, bm) * n
+                                   : std::max<int64_t>(G, (rows * 10 + 4 * G * bm) / (10 * bm)) * n;
+      return cdiv(tiles, slots);
+    };
+    return rounds(64) * 100 > rounds(128) * 135 ? PASS_STAGED : PASS_R64;
+  }
+  if (G == 1) {
+    const int64_t t = cdiv(rows, 128) * n;
+    if (cdiv(rows, 64) * n <= cus) return PASS_R64;
+    return t > cus && t <= slots ? PASS_STAGED : PASS_RING128;
+  }
+  const int64_t t64 = G * cdiv(rows, (int64_t)64 * G) * n;
+  return rows <= (int64_t)16 * G || t64 * 4 < (int64_t)11 * cus ? PASS_R64 : PASS_RING128;
+}
+
+// The 64-row tiles (gemm_r64.hip) take fp32 and, of the bf16 passes that others could take as well:
 // - grouped FFNs of at most 48 rows a group, hidden size below 4096: a
 //   128-row tile is then mostly padding.  64 groups, d 2048, F 1408, gate/up
 //   + down: 6 rows a group 146 + 68 us on the ring, 137 + 65 us on 64-row
@@ -126,15 +157,19 @@ inline PassKind pass_kind(int dtype, bool gateup, int64_t max_rows, int64_t like
   if (dtype != 1) return PASS_R64;
   const int NOUT = gateup ? ffn : d, K = gateup ? d : ffn, n_tiles = NOUT / (gateup ? 128 : 256);
   const bool stream = use_stream(dtype, max_rows, G, ffn, d);
+  if (stream) return G == 1 ? few_rows_kind(gateup, max_rows, NOUT, K) : PASS_STREAM;
+  const bool own = NOUT % (gateup ? 128 : 256) == 0, both = ffn % 128 == 0 && d % 256 == 0;
+  const int64_t ring_tiles = G * cdiv(max_rows, (int64_t)128 * G) * n_tiles;
+  // (where only the other pass's columns do not divide, short groups and passes
+  // that would split K do as if both did not)
+  if (!own || (!both && G > 1 && (ring_tiles < cus || max_rows <= (int64_t)48 * G)))
+    return odd_kind(gateup, likely_rows, G, NOUT, cus);
   if (G == 1) {
-    if (stream) return few_rows_kind(gateup, max_rows, NOUT, K);
-    if (r64_one_round(max_rows, NOUT / (gateup ? 64 : 128), K, cus, gateup || d % 256 == 0)) return PASS_R64;
-  } else if (!stream && max_rows <= (int64_t)48 * G && d < 4096) {
+    // (K limits it only where both widths divide, and the split ring is the choice)
+    if (r64_one_round(max_rows, NOUT / (gateup ? 64 : 128), both ? K : 64, cus)) return PASS_R64;
+  } else if (both && max_rows <= (int64_t)48 * G && d < 4096) {
     return PASS_R64;
   }
-  if (stream) return PASS_STREAM;
-  if (ffn % 128 != 0 || d % 256 != 0) return PASS_R64;
-  const int64_t ring_tiles = G * cdiv(max_rows, (int64_t)128 * G) * n_tiles;
   if (!r192_ok(likely_rows, G, K / 64, ring_tiles, cus)) return PASS_RING;
   return G > 1 || r192_pays(max_rows, n_tiles, cus) ? PASS_R192 : PASS_RING;
 }
@@ -152,36 +187,9 @@ inline PassKind pass_kind_fp8(bool gateup, int64_t max_rows, int G, int ffn, int
 // tiles when n is not a multiple of 256; never split).
 inline PassKind dense_kind(int dtype, int m, int n, int kdim, int cus) {
   if (dtype != 1 || r64_one_round(m, n / 128, kdim, cus, n % 256 == 0)) return PASS_R64;
-  const int64_t ring_tiles = cdiv(m, 128) * (n / (n % 256 == 0 ? 256 : 128));
-  return n % 256 == 0 && r192_ok(m, 1, kdim / 64, ring_tiles, cus) && r192_pays(m, n / 256, cus)
-             ? PASS_R192
-             : PASS_RING;
-}
-
-// Tile variant of the LDS-ring GEMMs, per pass: the interleaved 128 x 256
-// x 64 ring with eight waves (5) for every shape, except down passes whose
-// output width is a multiple of 128 but not of 256 (10: 128 x 128 tiles).
-// Measured against it and dropped (block steps, same box):
-// - a register-staged 256 x 256 kernel on dense gate/up (Llama-4-Scout-shaped
-//   shared expert 1317 -> 1232 us for the ring);
-// - 256-row tiles on routed passes, whose half-empty tail tiles waste MFMA
-//   work;
-// - 256 x 256 tiles (eight waves of 128 x 64, two 64 KB slots, 16 x 16 x 32
-//   MFMAs) on dense passes.  Alone they are faster on the DeepSeek-V3-shaped
-//   shared expert (gate/up 195 -> 184 us, down 119 -> 111 us), but their
-//   workgroups hold a whole CU's registers, and in the block, where the
-//   shared passes run beside the Dispatch stand-in copy, the copy's cost
-//   moves to whichever pass it overlaps: gate/up alone on them, 380 -> 230
-//   us, shared down 133 -> 399 us, step 3.78 -> 3.93 ms.  Llama-4-Scout-shaped
-//   shared gate/up (eight rounds of tiles) 1215 -> 1402 us;
-// - two K groups of four waves on the 128 x 256 tile (each wave 64 x 128
-//   over every other 32-wide K step, partial sums added in LDS): a quarter
-//   fewer LDS fragment reads, yet Llama-4-Scout-shaped routed gate/up 1390
-//   -> 1408 us, DeepSeek-V3-shaped down 977 -> 1050 us.
-// nout: output columns of the pass (F for gate/up, d for down).
-inline int tile_choice(bool down, int nout) {
-  if (down && nout % 256 != 0) return 10;   // the only down variant for such widths
-  return 5;
+  const int64_t ring_tiles = cdiv(m, 128) * (n / 256);
+  if (n % 256 != 0) return PASS_RING128;
+  return r192_ok(m, 1, kdim / 64, ring_tiles, cus) && r192_pays(m, n / 256, cus) ? PASS_R192 : PASS_RING;
 }
 
 }  // namespace

@@ -9,7 +9,7 @@ import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "..", "paper_2511_11505_amd", "csrc")
-R64, STREAM, RING, R192, SKINNY = range(5)
+R64, STREAM, RING, R192, SKINNY, STAGED, RING128 = range(7)
 CUS = 256   # of gfx950
 
 

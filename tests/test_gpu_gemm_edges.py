@@ -99,6 +99,30 @@ def test_dense_group_routes(rows, d, F, gu, dn):
     check_ffn("bf16", X, None, goff, wgu, wd, out)
 
 
+# columns that the 256-wide tiles do not divide, of this pass or of the other one:
+# every route (asserted), with groups around tile edges and empty ones
+ODD = [200, 0, 193, 1, 450, 64, 129, 563]
+
+
+@pytest.mark.parametrize("counts,d,F,gather,gu,dn", [
+    (ODD, 256, 1472, True, R.STAGED, R.R64), (ODD * 2, 1152, 192, False, R.R64, R.R64),
+    (ODD * 3, 1152, 192, True, R.R64, R.RING128), (ODD * 8, 384, 192, True, R.STAGED, R.RING128),
+    ([7700], 640, 192, False, R.R64, R.STAGED), ([2100], 1664, 1472, False, R.STAGED, R.RING128),
+    ([130] * 63 + [2], 1152, 512, True, R.R192, R.RING128), ([90] * 62 + [128, 3], 384, 512, True, R.RING, R.R64),
+    ([130] * 63 + [2], 2048, 320, True, R.STAGED, R.R192), ([130] * 63 + [2], 2048, 192, False, R.R64, R.RING)])
+def test_odd_width_routes(counts, d, F, gather, gu, dn):
+    M, G = sum(counts), len(counts)
+    assert (R.pass_kind(True, M, G, F, d), R.pass_kind(False, M, G, F, d)) == (gu, dn)
+    X, rows, goff, wgu, wd, n_src = ffn_case("bf16", counts, d, F, gather, seed=5)
+    out = torch.full((n_src, d), float("nan"), device=DEV).to(torch.bfloat16)
+    desc = L.make_desc(CONFIGS["tiny"].scaled(hidden=d, ffn=F, dtype="bf16"))
+    ws = torch.empty((L.fs_workspace_size(desc, L.FS_OP_GROUPED_FFN, M, F),), dtype=torch.uint8,
+                     device=DEV)
+    L.fs_grouped_expert_ffn(desc, G, F, X, rows, torch.from_numpy(goff).to(DEV), M, wgu, wd, out, ws)
+    torch.cuda.synchronize()
+    check_ffn("bf16", X, rows, goff, wgu, wd, out)
+
+
 # 192-row tiles: every tile height (128 to 192 in steps of 32 and the short
 # tiles below) and every largest height that a pass may choose (160, 192, 128),
 # groups of one to several equal tiles, one band and more of m-tiles, several

@@ -29,6 +29,10 @@ def test_pass_kernels_take_their_widths(gateup):
             assert rows <= min(64 * G, 4096) and n % 64 == 0 and K % 64 == 0
         elif kind == R.RING:
             assert n % (128 if gateup else 256) == 0 and K % 64 == 0
+        elif kind == R.RING128:
+            assert not gateup and n % 128 == 0 and K % 64 == 0
+        elif kind == R.STAGED:
+            assert n % (64 if gateup else 128) == 0 and K % 64 == 0
         elif kind == R.SKINNY:
             assert not gateup and G == 1 and rows <= 64 and K % 512 == 0 and n % 32 == 0
         else:
@@ -41,7 +45,7 @@ def test_pass_kernels_take_their_widths(gateup):
 def test_dense_kernels_take_their_widths():
     for m, _, kdim, n, cus in sizes(2, 20000):
         kind = R.dense_kind(m, n, kdim, cus=cus)
-        assert kind in (R.R64, R.RING) or (kind == R.R192 and n % 256 == 0 and kdim >= 256)
+        assert kind in (R.R64, R.RING128) or (n % 256 == 0 and (kind == R.RING or kind == R.R192 and kdim >= 256))
         assert R.dense_kind(m, n - 64 or 64, kdim, dtype="f32", cus=cus) == R.R64
 
 
@@ -99,6 +103,20 @@ def test_dense_group_routes(gateup, rows, d, F, kind):
 @pytest.mark.parametrize("m,n,k,kind", [
     (640, 5120, 640, R.R64), (800, 5120, 640, R.RING), (1300, 5120, 640, R.RING),
     (1300, 5120, 384, R.RING), (1700, 5120, 640, R.R192), (2400, 2048, 2048, R.RING),
-    (1300, 4096, 3072, R.RING), (4096, 3072, 3072, R.RING), (1700, 1152, 1024, R.R64), (2000, 1152, 1024, R.RING)])
+    (1300, 4096, 3072, R.RING), (4096, 3072, 3072, R.RING), (1700, 1152, 1024, R.R64), (2000, 1152, 1024, R.RING128)])
 def test_dense_linear_routes(m, n, k, kind):
     assert R.dense_kind(m, n, k) == kind
+
+
+# columns that the 256-wide tiles do not divide, of this pass or of the other:
+# (rows, groups, d, F), gate/up and down
+@pytest.mark.parametrize("rows,G,d,F,gu,dn", [
+    (24 * 108, 24, 1408, 960, R.STAGED, R.R64), (64 * 300, 64, 1664, 2496, R.STAGED, R.RING128),
+    (16 * 180, 16, 640, 1472, R.STAGED, R.R64), (64 * 4, 64, 1664, 2496, R.R64, R.R64),
+    (64 * 130, 64, 2944, 1408, R.R192, R.RING128), (64 * 90, 64, 2944, 1408, R.RING, R.RING128),
+    (2743, 24, 2304, 1088, R.R64, R.RING128), (40 * 2, 40, 896, 1024, R.R64, R.R64),
+    (64 * 130, 64, 2048, 960, R.STAGED, R.R192), (16 * 48, 16, 2048, 960, R.STREAM, R.STREAM),
+    (333, 1, 1408, 704, R.R64, R.R64), (3000, 1, 1664, 2496, R.STAGED, R.STAGED),
+    (700, 1, 4480, 1536, R.R64, R.RING128), (3000, 1, 4480, 1536, R.R192, R.RING128)])
+def test_odd_width_routes(rows, G, d, F, gu, dn):
+    assert (R.pass_kind(True, rows, G, F, d), R.pass_kind(False, rows, G, F, d)) == (gu, dn)
