@@ -145,16 +145,26 @@ inline PassKind odd_kind(bool gateup, int64_t rows, int G, int NOUT, int cus) {
   return rows <= (int64_t)16 * G || t64 * 4 < (int64_t)11 * cus ? PASS_R64 : PASS_RING128;
 }
 
-// The 64-row tiles (gemm_r64.hip) take fp32 and, of the bf16 passes that others could take as well:
-// - grouped FFNs of at most 48 rows a group, hidden size below 4096: a
-//   128-row tile is then mostly padding.  64 groups, d 2048, F 1408, gate/up
-//   + down: 6 rows a group 146 + 68 us on the ring, 137 + 65 us on 64-row
-//   tiles; 31 rows 160 + 71 and 148 + 70; but 66 rows 169 + 76 and 177 + 95,
-//   and 32 groups of 16 rows, d 7168, F 2048: 295 + 163 and 301 + 179;
-// - one dense group as above.
+// Grouped passes of short groups (hidden size below 4096) on the 64-row tiles, since
+// a 128-row tile is mostly padding: gate/up up to 40 rows a group and K of 2048,
+// down up to 32 rows and K of 1024, or where the ring would split a K below 4096.  us,
+// weights from HBM, ring and 64-row tiles: gate/up of 64 groups, d 2048, F 1408: 12
+// rows a group 142 and 136, 44 rows 150 and 144, but of 24, d 1280, F 2560, 44 rows 65
+// and 71; of 60, d 2560, F 1408: 163 and 166, 171 and 175; of 128, d 512, F 384: 28 and
+// 21, 28 and 25; down of the first 68 and 71, 71 and 80, of the last 15.2 and 13.5, 16.8
+// and 18.4; of 24, d 1280, F 2560 (120 ring tiles): 4 rows 42 and 44, 24 rows 50 and 44,
+// 44 rows 59 and 49; 32 groups of 12 rows, d 1024, F 4096 (128 ring tiles), both passes
+// 159 with the ring's down, 167 with 64-row tiles.
+inline bool short_groups(bool gateup, int64_t max_rows, int G, int K, int d, int64_t ring_tiles, int cus) {
+  if (max_rows > (int64_t)48 * G || d >= 4096) return false;
+  if (gateup) return max_rows <= (int64_t)40 * G && K <= 2048;
+  return (max_rows <= (int64_t)32 * G && K <= 1024) ||
+         (ring_tiles < cus && max_rows >= (int64_t)12 * G && K < 4096);
+}
+
 inline PassKind pass_kind(int dtype, bool gateup, int64_t max_rows, int64_t likely_rows, int G,
                           int ffn, int d, int cus) {
-  if (dtype != 1) return PASS_R64;
+  if (dtype != 1) return PASS_R64;   // every fp32 pass
   const int NOUT = gateup ? ffn : d, K = gateup ? d : ffn, n_tiles = NOUT / (gateup ? 128 : 256);
   const bool stream = use_stream(dtype, max_rows, G, ffn, d);
   if (stream) return G == 1 ? few_rows_kind(gateup, max_rows, NOUT, K) : PASS_STREAM;
@@ -167,7 +177,7 @@ inline PassKind pass_kind(int dtype, bool gateup, int64_t max_rows, int64_t like
   if (G == 1) {
     // (K limits it only where both widths divide, and the split ring is the choice)
     if (r64_one_round(max_rows, NOUT / (gateup ? 64 : 128), both ? K : 64, cus)) return PASS_R64;
-  } else if (both && max_rows <= (int64_t)48 * G && d < 4096) {
+  } else if (both && short_groups(gateup, max_rows, G, K, d, ring_tiles, cus)) {
     return PASS_R64;
   }
   if (!r192_ok(likely_rows, G, K / 64, ring_tiles, cus)) return PASS_RING;

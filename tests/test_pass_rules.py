@@ -120,3 +120,12 @@ def test_dense_linear_routes(m, n, k, kind):
     (700, 1, 4480, 1536, R.R64, R.RING128), (3000, 1, 4480, 1536, R.R192, R.RING128)])
 def test_odd_width_routes(rows, G, d, F, gu, dn):
     assert (R.pass_kind(True, rows, G, F, d), R.pass_kind(False, rows, G, F, d)) == (gu, dn)
+
+
+@pytest.mark.parametrize("per,G,d,F,gu,dn", [
+    (12, 64, 2048, 1408, R.R64, R.RING), (40, 64, 2048, 1408, R.R64, R.RING), (41, 64, 2048, 1408, R.RING, R.RING),
+    (24, 60, 2560, 1408, R.RING, R.RING), (24, 128, 512, 384, R.R64, R.R64), (36, 128, 512, 384, R.R64, R.RING),
+    (4, 24, 1280, 2560, R.R64, R.RING), (24, 24, 1280, 2560, R.R64, R.R64), (16, 32, 7168, 2048, R.RING, R.RING),
+    (12, 32, 1024, 4096, R.R64, R.RING)])
+def test_short_group_routes(per, G, d, F, gu, dn):
+    assert (R.pass_kind(True, per * G, G, F, d), R.pass_kind(False, per * G, G, F, d)) == (gu, dn)
