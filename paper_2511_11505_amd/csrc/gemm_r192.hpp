@@ -213,13 +213,14 @@ __global__ __launch_bounds__(256, 1) void gemm_r192_kernel(
     dma4_at(rows + it.row_base + it.m0 + min(wave * 64 + lane, it.rows_t - 1),
             lds_addr(s_rows) + wave * 256);
   };
-  // FP8: the scales of an item's rows (gate/up: its row indices are still in
-  // s_rows) and weight rows, the latter in the order of the B tile's columns
+  // FP8: the scales of an item's rows and weight rows, the latter in the order
+  // of the B tile's columns.  Gate/up: a wave reads only the row indices that
+  // it copied itself (past the item's end they repeat the last row), since
+  // another wave may already have replaced its own by the next item's.
   auto fetch_scales = [&](const Item& it) {
-    int r = min(wave * 64 + lane, it.rows_t - 1);
-    r = (MODE == MODE_GATEUP && rows) ? s_rows[r] : it.row_base + it.m0 + r;
-    dma4_at(sA + r, lds_addr(s_sa) + wave * 256);
     const int c = wave * 64 + lane;
+    const int r = (MODE == MODE_GATEUP && rows) ? s_rows[c] : it.row_base + it.m0 + min(c, it.rows_t - 1);
+    dma4_at(sA + r, lds_addr(s_sa) + wave * 256);
     const float* sg = sB + (size_t)it.g * (MODE == MODE_GATEUP ? 2 * NOUT : NOUT) + it.n0;
     dma4_at(sg + (MODE == MODE_GATEUP && c >= 128 ? NOUT + c - 128 : c), lds_addr(s_sb) + wave * 256);
   };
