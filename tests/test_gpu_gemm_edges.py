@@ -130,11 +130,16 @@ def test_odd_width_routes(counts, d, F, gather, gu, dn):
 TALL = [192, 193, 130, 0, 97, 384, 385, 5, 161, 577, 224, 256]
 
 
-@pytest.mark.parametrize("counts,d,F,gather,slack", [
-    (TALL, 2048, 1408, True, 0), (TALL, 512, 3072, False, 31), (TALL * 2, 256, 2816, True, 0),
-    ([2048], 768, 2048, False, 0), ([3500, 1], 1280, 1408, True, 5), ([4100], 256, 1024, False, 0),
-    ([300] * 8 + [50], 4096, 2048, True, 3)])
-def test_ffn_tall_tiles(counts, d, F, gather, slack):
+@pytest.mark.parametrize("counts,d,F,gather,slack,gu,dn", [
+    (TALL, 2048, 1408, True, 0, 1, 0), (TALL, 512, 3072, False, 31, 1, 0), (TALL * 2, 256, 2816, True, 0, 1, 0),
+    ([2048], 768, 2048, False, 0, 1, 0), ([3500, 1], 1280, 1408, True, 5, 1, 0), ([4100], 256, 1024, False, 0, 1, 0),
+    ([300] * 8 + [50], 4096, 2048, True, 3, 1, 1),
+    # down passes, scattered and in order: K of four blocks, several tiles a workgroup
+    (TALL, 2816, 512, True, 0, 0, 1), (TALL * 2, 2816, 768, True, 9, 1, 1), (TALL, 3072, 256, False, 0, 0, 1),
+    ([370] * 8 + [100], 4096, 256, True, 0, 0, 1), ([2500, 3], 3328, 640, True, 0, 0, 1), ([4100], 2304, 512, False, 0, 0, 1)])
+def test_ffn_tall_tiles(counts, d, F, gather, slack, gu, dn):
+    bound, G = sum(counts) + slack, len(counts)
+    assert [R.pass_kind(g, bound, G, F, d) == R.R192 for g in (True, False)] == [gu, dn]
     X, rows, goff, wgu, wd, n_src = ffn_case("bf16", counts, d, F, gather, seed=7)
     bound = int(goff[-1]) + slack
     out = torch.full((n_src, d), float("nan"), device=DEV).to(torch.bfloat16)
@@ -161,24 +166,31 @@ def test_dense_linear_edges(dtype, m, n, kd):
     assert rel_err(out, oracle.dense_linear(f64(a), f64(w))) <= TOL[dtype]
 
 
+def quant(t):
+    c = torch.empty(t.shape, dtype=torch.uint8, device=DEV)
+    s = torch.empty(t.shape[:-1], dtype=torch.float32, device=DEV)
+    L.fs_quantize_fp8(L.FS_BF16, s.numel(), t.shape[-1], t, c, s)
+    return c, s
+
+
 # FP8 on the 192-row tiles (heights 128 and 192, odd and even K block counts)
 # against the fragment-ordered kernel on the same codes: H is the same bits;
 # the down pass's fp32 sums may round differently in the last place, so an
 # output differs by one bf16 step at most (2^-7 of its value), or, where the
-# sum cancels, by the fp32 rounding of its terms (2048 2^-24 of the rms bounds
-# it: 1.3e-4).
-@pytest.mark.parametrize("counts,d,F,gather", [(TALL, 2048, 1408, True), (TALL * 2, 512, 2816, False),
-                                               ([2050], 768, 2048, False), ([3000, 1], 1280, 1408, True)])
-def test_ffn_fp8_tall_tiles(counts, d, F, gather):
+# sum cancels, by the fp32 rounding of its F terms (F 2^-24 of the rms bounds
+# it).
+@pytest.mark.parametrize("counts,d,F,gather,gu,dn", [
+    (TALL, 2048, 1408, True, 1, 0), (TALL * 2, 512, 2816, False, 1, 0), ([2050], 768, 2048, False, 1, 0),
+    ([3000, 1], 1280, 1408, True, 1, 0),
+    # down passes, scattered and in order: K of four blocks, several tiles a workgroup
+    # (gate/up passes that split K would not give the same bits of H)
+    (TALL * 3, 2816, 512, True, 1, 1), (TALL * 2, 2816, 768, True, 1, 1), (TALL * 3, 1024, 640, False, 1, 1),
+    ([300] * 8 + [50], 4096, 1280, True, 1, 1), ([4100], 2304, 1024, False, 1, 1)])
+def test_ffn_fp8_tall_tiles(counts, d, F, gather, gu, dn):
+    kinds = [R.pass_kind_fp8(g, sum(counts), len(counts), F, d) for g in (True, False)]
+    assert [k == R.R192 for k in kinds] == [gu, dn]
     X, rows, goff, wgu, wd, n_src = ffn_case("bf16", counts, d, F, gather, seed=9)
     G, M = len(counts), int(goff[-1])
-
-    def quant(t):
-        c = torch.empty(t.shape, dtype=torch.uint8, device=DEV)
-        s = torch.empty(t.shape[:-1], dtype=torch.float32, device=DEV)
-        L.fs_quantize_fp8(L.FS_BF16, s.numel(), t.shape[-1], t, c, s)
-        return c, s
-
     (xc, xs), (gc, gs), (dc, ds) = quant(X), quant(wgu), quant(wd)
     desc = L.make_desc(CONFIGS["tiny"].scaled(hidden=d, ffn=F, dtype="bf16"))
     ws = torch.empty((L.fs_workspace_size(desc, L.FS_OP_GROUPED_FFN_FP8, M, F),), dtype=torch.uint8,
@@ -194,10 +206,41 @@ def test_ffn_fp8_tall_tiles(counts, d, F, gather):
     assert torch.equal(h_out, H())
     at = rows.long() if gather else torch.arange(M, device=DEV)
     o, r = out[at].double(), ref[at].double()
-    assert torch.all((o - r).abs() <= 2.0 ** -7 * r.abs() + 1.3e-4 * r.square().mean().sqrt())
+    assert torch.all((o - r).abs() <= 2.0 ** -7 * r.abs() + F * 2.0 ** -24 * r.square().mean().sqrt())
     rest = torch.ones(n_src, dtype=torch.bool, device=DEV)
     rest[at] = False
     assert out[rest].isnan().all()
+
+
+# the ring running on from tile to tile: more tiles than workgroups, gathered rows
+# through scalar loads, K of 4 and 8 blocks (FP8: 4), groups too short for the
+# 192-row tiles
+@pytest.mark.parametrize("d", [256, 512])
+@pytest.mark.parametrize("fp8", [False, True])
+def test_ffn_ring_many_tiles(d, fp8):
+    counts, F = [100] * 31 + [0, 1, 111, 0] + [97] * 31, 1408
+    M, G = sum(counts), len(counts)
+    kind = R.pass_kind_fp8(True, M, G, F, d) if fp8 else R.pass_kind(True, M, G, F, d)
+    assert kind == R.RING and G * (F // 128) > 2 * R.CUS
+    X, rows, goff, wgu, wd, n_src = ffn_case("bf16", counts, d, F, True, seed=11)
+    desc = L.make_desc(CONFIGS["tiny"].scaled(hidden=d, ffn=F, dtype="bf16"))
+    go = torch.from_numpy(goff).to(DEV)
+    out = torch.full((n_src, d), float("nan"), device=DEV).to(torch.bfloat16)
+    op = L.FS_OP_GROUPED_FFN_FP8 if fp8 else L.FS_OP_GROUPED_FFN
+    ws = torch.empty((L.fs_workspace_size(desc, op, M, F),), dtype=torch.uint8, device=DEV)
+    if not fp8:
+        L.fs_grouped_expert_ffn(desc, G, F, X, rows, go, M, wgu, wd, out, ws)
+        torch.cuda.synchronize()
+        check_ffn("bf16", X, rows, goff, wgu, wd, out)
+        return
+    (xc, xs), (gc, gs), (dc, ds) = quant(X), quant(wgu), quant(wd)
+    L.fs_grouped_expert_ffn_fp8(desc, G, F, xc, xs, rows, go, M, gc, gs, dc, ds, out, ws)
+    h = ws[:2 * M * F].clone()
+    ref = torch.empty_like(out)
+    L.fs_grouped_expert_ffn_fp8_fo(desc, G, F, xc, xs, rows, go, M, fragment_ordered_fp8(gc), gs,
+                                   fragment_ordered_fp8(dc), ds, ref, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(h, ws[:2 * M * F])   # the gate/up pass, bit for bit
 
 
 # a row bound of all token slots over the 8 experts of 64 that are here: both

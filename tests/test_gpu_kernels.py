@@ -240,10 +240,10 @@ def test_grouped_ffn(dtype, G, d, F, gather):
 @pytest.mark.parametrize("counts,d,F,gather", [([12000, 0, 9001, 1, 8000, 11111], 256, 128, True),
                                                ([12000, 0, 9001, 1, 8000, 11111], 512, 256, False)])
 def test_grouped_ffn_many_tiles(counts, d, F, gather):
-    """More 128-row tiles than workgroups, so the interleaved ring runs on
-    from tile to tile (the last blocks of a tile prefetch the next tile's
-    first ones; gathered rows through scalar loads), with K rings of 2, 4
-    and 8 blocks; element by element against the oracle."""
+    """Groups of thousands of rows and more tiles than workgroups: passes of 4
+    and 8 K blocks on the 192-row tiles, whose copies run on from tile to tile
+    (gathered rows among them), and a down pass of 2 blocks on the interleaved
+    ring, which does the same; element by element against the oracle."""
     counts = np.array(counts)
     G, M = len(counts), int(counts.sum())
     goff = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
