@@ -257,7 +257,8 @@ fs_status fs_local_rows(const fs_moe_desc* desc, const int32_t* expert_offsets,
 /* Grouped SwiGLU expert FFN (Section 2.1, MLP^j read as SwiGLU): for each
  * group g and its rows X_g, Y_g = (SiLU(X_g Wg^T) * (X_g Wu^T)) Wd^T.
  * bf16 runs on MFMA with fp32 accumulation and the hidden activation
- * rounded to bf16; fp32 runs on the vector ALUs.
+ * rounded to bf16; fp32 runs on the fp32 matrix cores (fp32 multiply and
+ * accumulate).
  *   n_groups      groups (local experts, or 1 for merged shared experts)
  *   ffn           F of every group
  *   in_rows       [*, d] dtype: row i of the grouped order is

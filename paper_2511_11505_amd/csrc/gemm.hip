@@ -200,21 +200,18 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_kernel(
   }
 }
 
-// ---------------------------------------------------------------- bf16 MFMA, DMA ring
-// BM x BN x 64 tiles, four waves (2 x 2), each wave BM/2 x BN/2 through
-// v_mfma_f32_32x32x16_bf16.  Operand tiles stream into an LDS ring of
-// STAGES slots with direct global->LDS 16-byte loads (no staging
-// registers), STAGES-1 K blocks ahead of the MFMAs.  A 64-element K row is
-// 8 chunks of 16 bytes; chunk c of row r sits at position c ^ ((r / 2) % 8):
-// the LDS serves a ds_read_b128 sixteen lanes at a time over 64 banks, and
-// sixteen consecutive rows then cover all 64 banks once.  Rows past the end of a group load a valid row of the
-// group instead (a DMA cannot write zeros); their results are never stored.
-// The epilogue stages the output tile through LDS so that global stores are
-// whole 16-byte row chunks.
-
 // ---------------------------------------------------------------- bf16 MFMA, interleaved
-// Same tiles, ring and swizzle as above, with the memory work hidden under
-// the MFMAs by a rolling pipeline over 16-wide K steps.  Each step first
+// BM x BN x BK tiles.  Operand tiles stream into an LDS ring of STAGES slots
+// with direct global->LDS 16-byte loads (no staging registers), STAGES - 1 K
+// blocks ahead of the MFMAs.  A 64-element K row is 8 chunks of 16 bytes; chunk
+// c of row r sits at position c ^ ((r / 2) % 8): the LDS serves a ds_read_b128
+// sixteen lanes at a time over 64 banks, and sixteen consecutive rows then
+// cover all 64 banks once.  Rows past the end of a group load a valid row of
+// the group instead (a DMA cannot write zeros); their results are never
+// stored.
+//
+// The memory work is hidden under the MFMAs by a rolling pipeline over the K
+// steps of a block (16 wide, or 32 with M16).  Each step first
 // issues the LDS reads of the next step's fragments (double-buffered
 // registers), then its own MFMAs; the DMAs of the block two ahead are spread
 // over the first steps of a block, one after each of the first MFMAs.  The

@@ -1,5 +1,5 @@
-// The bf16 down pass of gemm_r192.hpp (a file of its own: each takes about a
-// minute to compile).
+// The bf16 down pass of gemm_r192.hpp (a file of its own, so that the two
+// compile side by side: 21 s each).
 #include "gemm_r192.hpp"
 
 namespace fs {

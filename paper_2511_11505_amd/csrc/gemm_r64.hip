@@ -1,14 +1,17 @@
 // Grouped SwiGLU FFN passes and dense linears on 64-row tiles: every fp32
-// pass, and the bf16 passes whose groups are short or whose widths the
-// 128-row rings do not divide (Section 2.1).
+// pass, and the bf16 passes whose groups are short, whose one dense group makes
+// few tiles, or whose columns the ring's tiles do not divide (Section 2.1;
+// pass_rules.hpp says which).
 //
 // A workgroup of four waves owns 64 rows x BN weight rows (128, or 64 where
-// 128 would give too few tiles) and walks K in 128-byte blocks (32 floats, 64
-// bf16) through a three-slot LDS ring filled by direct global->LDS copies two
-// blocks ahead; two (BN 128) or three workgroups fit a CU, so one computes
-// while another waits.  16-byte chunk c of staged row r sits at position
-// c ^ ((r / 2) % 8), so a 16-byte LDS read by sixteen consecutive rows covers
-// every bank once.  Lane l reads row l % 16, chunk l / 16 of a 64-byte half
+// 128 would give too few tiles) and walks K in blocks of ROWB bytes a row
+// through a ring of NST LDS slots filled by direct global->LDS copies NST - 1
+// blocks ahead: 128 bytes (32 floats, 64 bf16) in three slots, where two (BN
+// 128) or three workgroups fit a CU and one computes while another waits; 256
+// bytes in four slots, or 128 in eight, where there is at most one workgroup
+// per CU.  16-byte chunk c of staged row r sits at position c ^ ((r / 2) % 8)
+// (256-byte rows: c ^ (r % 16)), so a 16-byte LDS read by sixteen consecutive
+// rows covers every bank once.  Lane l reads row l % 16, chunk l / 16 of a 64-byte half
 // block: one v_mfma_f32_16x16x32_bf16 operand, or the operands of four
 // v_mfma_f32_16x16x4_f32 (both operands use the same K order).  fp32
 // multiplies and accumulates in fp32, at twice the rate of unpacked vector
@@ -28,7 +31,7 @@
 // per thread): 64 groups of about 48 rows, d 2048, F 1408: gate/up 734 -> 415
 // us, down 322 -> 216 us (MFMA busy 80% of the cycles a CU has work; 8% of
 // the rest is the last round of tiles); 512 dense rows, F 2816: gate/up 226
-// -> 124 us, down 152 -> 65 us.  The block of those shapes 1491 -> 822 us.
+// -> 124 us, down 152 -> 65 us.  The block of those shapes 1496 -> 847 us.
 #include <algorithm>
 #include <type_traits>
 
@@ -101,7 +104,7 @@ __global__ __launch_bounds__(256, OCC) void gemm_r64_kernel(
     const int row_base = s_goff[g], rows_g = s_goff[g + 1] - row_base;
     const T* Bg = B + (size_t)g * bstride;
 
-    // sources of this wave's DMAs (8 rows of 128 bytes each); rows past the
+    // sources of this wave's DMAs (RPD rows of ROWB bytes each); rows past the
     // group's end load its last row and are never stored
     const T *pa[A_LD], *pb[B_LD];
 #pragma unroll
