@@ -2,10 +2,12 @@
 // groups of a hundred rows and more (Section 2.1, prefill).
 //
 // What bounds the 128 x 256 ring (gemm.hip) is not the matrix cores but the
-// stream of L2 requests that fills its LDS: about 100 G requests/s over the
-// chip, 48 KB per 64-wide K block of a tile (one L2 request per 128-byte
-// row), its copies alone taking as long as the pass; the same loop without
-// copies runs 1.8 times faster.  (A first version of this kernel with 64-byte
+// stream of L2 requests that fills its LDS: 48 KB per 64-wide K block of a tile
+// (one L2 request per 128-byte row), its copies alone taking as long as the
+// pass; in a timing variant the same loop without copies ran 1.8 times faster.
+// (This kernel's counters: 81 G requests/s and the matrix cores 53% busy on 16
+// groups of about 512 rows, d 5120, F 8192, gate/up; 96 G/s and 71% on 8192 dense
+// rows.)  (A first version of this kernel with 64-byte
 // rows, 256 x 256 x 32 tiles, made as many requests for half the bytes and
 // was no faster than the ring.)  So the tile is taller, and the wave tile
 // larger: four waves (2 x 2), one per SIMD, each up to 96 x 128 through
@@ -37,8 +39,8 @@
 //            into LDS bring at the tile's start.
 //
 // Measured (us, ring -> this): 8192 rows, d 5120, F 8192, dense gate/up 1228
-// -> 998 (1.38 PFLOP/s, as fast as the vendor library's dense kernel), down
-// 590 -> 546; 16 groups of about 512 rows of the same: 1410 -> 1290 and 706
+// -> 998 (1.38 PFLOP/s; on another box 1014, the vendor library's dense kernel
+// 921), down 590 -> 546; 16 groups of about 512 rows of the same: 1410 -> 1290 and 706
 // -> 641; 32 groups of 1024 rows, d 7168, F 2048: 1755 -> 1690 and 978 ->
 // 829, FP8 916 -> 860 and 565 -> 470; 64 groups of 384 rows, d 2048, F 1408:
 // 347 -> 298 and 199 -> 176.

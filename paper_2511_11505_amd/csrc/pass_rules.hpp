@@ -64,12 +64,13 @@ inline bool r192_pays(int64_t rows, int n_tiles, int cus, int unit = 32) {
 // K).  64 groups, d 2048, F 1408, gate/up + down: 96 rows a group 169 + 79 us
 // on the ring, 168 + 81 us on these tiles; 128 rows 216 + 114 and 180 + 87;
 // 384 rows 367 + 209 and 330 + 197.  32 groups of 1024 rows, d 7168, F 2048:
-// 1755 + 978 and 1690 + 829 (FP8 916 + 565 and 860 + 470).  One group of 8192 rows, gate/up of d 5120,
-// F 8192: 1228 -> 998 us (1.38 PFLOP/s).
-// rows are the likely ones where the bound is loose: 1300 replicated tokens, 160
-// experts top-6, 20 of them here, d 5120 (a bound of 390 rows a group, 49 of
-// them real): layer 452 us when the bound decides, 449 us so (441 to 446 us
-// before there were 192-row tiles); 2000 tokens 508 and 504 us.
+// 1755 + 978 and 1690 + 829 (FP8 916 + 565 and 860 + 470).  One group of 8192
+// rows, gate/up of d 5120, F 8192: 1228 -> 998 us (1.38 PFLOP/s).
+// rows are the likely ones (likely_rows) where the bound is loose: replicated
+// tokens, 160 experts top-6, 20 of them here, d 5120, the whole layer (us, ring |
+// so): 1300 tokens (a bound of 390 rows a group, 49 of them real; the ring both
+// times) 458 | 458, 2000 tokens 523 | 521, 4096 tokens (154 real rows, these
+// tiles) 711 | 665.  Deciding by the bound took 3 us more at 1300 tokens.
 inline bool r192_ok(int64_t rows, int G, int k_blocks, int64_t ring_tiles, int cus) {
   return rows >= (int64_t)112 * G && ring_tiles >= cus && k_blocks >= 4;
 }
