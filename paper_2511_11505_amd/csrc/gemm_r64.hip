@@ -29,9 +29,9 @@
 //
 // Measured, fp32, against 64 x 64 tiles on the vector ALUs (4 x 4 outputs
 // per thread): 64 groups of about 48 rows, d 2048, F 1408: gate/up 734 -> 415
-// us, down 322 -> 216 us (MFMA busy 80% of the cycles a CU has work; 8% of
-// the rest is the last round of tiles); 512 dense rows, F 2816: gate/up 226
-// -> 124 us, down 152 -> 65 us.  The block of those shapes 1496 -> 847 us.
+// us, down 322 -> 216 us (MFMA busy 66% and 56% of all cycles, by its counters);
+// 512 dense rows, F 2816: gate/up 226 -> 124 us, down 152 -> 65 us.  The block of
+// those shapes 1496 -> 847 us.
 #include <algorithm>
 #include <type_traits>
 

@@ -185,7 +185,11 @@ inline PassKind pass_kind(int dtype, bool gateup, int64_t max_rows, int64_t like
   return G > 1 || r192_pays(max_rows, n_tiles, cus) ? PASS_R192 : PASS_RING;
 }
 
-// An FP8 pass: the ring or the 192-row tiles.
+// An FP8 pass: the ring or the 192-row tiles, whose line in bf16 holds in FP8 too.
+// The FFN of groups of 112, 128, 160 and 390 rows (us, ring | 192-row tiles): 64
+// groups, d 2048, F 1408: 169 | 155, 170 | 165, 196 | 192, 337 | 317; 32 groups,
+// d 7168, F 2048: 350 | 317, 349 | 343, 413 | 393, 716 | 627; 16 groups, d 5120, F
+// 8192: 485 | 464, 580 | 480, 580 | 534, 986 | 893.  Shorter ones were not tried.
 inline PassKind pass_kind_fp8(bool gateup, int64_t max_rows, int G, int ffn, int d, int cus) {
   const int NOUT = gateup ? ffn : d, K = gateup ? d : ffn, n_tiles = NOUT / (gateup ? 128 : 256);
   const int64_t ring_tiles = G * cdiv(max_rows, (int64_t)128 * G) * n_tiles;
